@@ -1461,10 +1461,13 @@ __global__ __launch_bounds__(256) void k_destagger(DestaggerArgs A)
 // over the extended primary grid (rows k < 0 take parity * row -1-k: m_A for the rho and theta
 // components, m_S for the z ones; rows >= nr and columns outside the grid are 0), summed over the modes.
 // Blocks take GATHER_BLOCK consecutive samples; two blocks share a CU, so one block's loads overlap the
-// other's arithmetic.  When the nodes and rows their shapes touch (rows below the axis read rows 0 and 1)
-// fit GATHER_TILE values over all modes and components, the block first copies them into LDS (as FP64)
-// and every sample reads its 16 nodes per mode and component from there; position-ordered samples make
-// that footprint small.  Otherwise the samples read the planes directly.
+// other's arithmetic.  A sample reads 16 nodes of each of the 6 planes of every mode, so the block first copies
+// the nodes and rows its samples' shapes touch (rows below the axis read rows 0 and 1) into an LDS tile of
+// GATHER_TILE values (as FP64): all planes at once where they fit -- position-ordered samples make the
+// footprint small -- else as many planes per pass as do.  Only a footprint beyond the tile by itself is read
+// from the planes directly, where the scattered 16-byte reads bound the kernel: a bunch 100 rows wide, whose
+// 18 planes do not fit together (10^6 samples, three modes of a 4096 x 512 grid, FP64), took 537 us that way and
+// takes 190 us in four passes.
 constexpr int GATHER_BLOCK = 512, GATHER_TILE = 4096;
 template <typename R>
 __global__ __launch_bounds__(GATHER_BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void k_gather(GatherArgs A)
@@ -1499,17 +1502,11 @@ __global__ __launch_bounds__(GATHER_BLOCK) __attribute__((amdgpu_waves_per_eu(4)
     // groups of 16-byte reads, and the lanes of a wave (samples at about the same z) differ mostly in row.
     const bool any = fp[1] >= fp[0] && fp[3] >= fp[2];  // some sample of the block touches the grid
     const int tz = any ? fp[1] - fp[0] + 1 : 0, tr = any ? fp[3] - fp[2] + 1 : 0, ts = tz | 1;
-    const bool use_tile = any && (int64_t)ts * tr * 6 * A.nprob <= GATHER_TILE;  // uniform
-    if (use_tile) {
-        const int per = tz * tr, total = per * 6 * A.nprob;
-        for (int e = threadIdx.x; e < total; e += GATHER_BLOCK) {
-            const int pc = e / per, cell = e % per, k = cell / tz, i = cell % tz;
-            const V v = ((const V *)A.plane[pc / 6][pc % 6])[(size_t)(fp[2] + k) * A.nz + fp[0] + i];
-            tile[(pc * tr + k) * ts + i] = double2{(double)v.x, (double)v.y};
-        }
-        __syncthreads();
-    }
-    if (!live) return;
+    // planes copied per pass: all of them where they fit, else as many as do (0: none, the samples read the
+    // planes directly)
+    const int64_t per_plane = (int64_t)ts * tr;
+    const int npl = 6 * A.nprob, fit = any ? (int)(per_plane * npl <= GATHER_TILE ? npl : GATHER_TILE / per_plane) : 0;
+    const bool use_tile = fit > 0;  // uniform
     // e^(i theta) from the position itself (theta = 0 on the axis); e^(i m theta) is its m-th power
     const double c1 = rho > 0.0 ? x / rho : 1.0, s1 = rho > 0.0 ? y / rho : 0.0;
     const double zc = z / A.dz, rc = rho / A.dr - 0.5;
@@ -1531,27 +1528,47 @@ __global__ __launch_bounds__(GATHER_BLOCK) __attribute__((amdgpu_waves_per_eu(4)
         row[v] = min(max(q, rlo), rhi) - rlo;
         below[v] = k < 0;
     }
+    // the planes in order of mode, then component; cr + i ci = e^(i m theta) of the current mode
+    double acc[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0}, cr = 1.0, ci = 0.0;
+    const int step = use_tile ? fit : npl;
 #pragma unroll 1
-    for (int c = 0; c < 6; ++c) {
-        double acc = 0.0;
-        for (int p = 0; p < A.nprob; ++p) {
-            const int m = A.m[p];
+    for (int q0 = 0; q0 < npl; q0 += step) {
+        const int q1 = min(npl, q0 + step);
+        if (use_tile) {
+            if (q0) __syncthreads();  // the last pass's reads are done
+            for (int q = q0; q < q1; ++q) {
+                const V *f = (const V *)A.plane[q / 6][q % 6] + (size_t)fp[2] * A.nz + fp[0];
+                for (int e = threadIdx.x; e < tz * tr; e += GATHER_BLOCK) {
+                    const int k = e / tz, i = e % tz;
+                    const V v = f[(size_t)k * A.nz + i];
+                    tile[((q - q0) * tr + k) * ts + i] = double2{(double)v.x, (double)v.y};
+                }
+            }
+            __syncthreads();
+        }
+        if (!live) continue;
+#pragma unroll 1
+        for (int q = q0; q < q1; ++q) {
+            const int p = q / 6, c = q % 6, m = A.m[p];
+            if (c == 0) {
+                cr = 1.0;
+                ci = 0.0;
+                for (int j = 0; j < (m < 0 ? -m : m); ++j) {
+                    const double t = cr * c1 - ci * s1;
+                    ci = cr * s1 + ci * c1;
+                    cr = t;
+                }
+                if (m < 0) ci = -ci;
+            }
             const double pS = (m % 2 == 0) ? 1.0 : -1.0, pA = ((m > 1 ? m - 1 : 1 - m) % 2 == 0) ? 1.0 : -1.0;
             const double par = (c == 2 || c == 5) ? pS : pA;
-            double cr = 1.0, ci = 0.0;
-            for (int j = 0; j < (m < 0 ? -m : m); ++j) {
-                const double t = cr * c1 - ci * s1;
-                ci = cr * s1 + ci * c1;
-                cr = t;
-            }
-            if (m < 0) ci = -ci;
             double re = 0.0, im = 0.0;
 #pragma unroll
             for (int a = 0; a < 4; ++a) {
                 const double wa = below[a] ? par * wr[a] : wr[a];
                 double v[8];
                 if (use_tile) {
-                    const double2 *t = tile + ((p * 6 + c) * tr + row[a]) * ts;
+                    const double2 *t = tile + ((q - q0) * tr + row[a]) * ts;
 #pragma unroll
                     for (int b = 0; b < 4; ++b) {
                         const double2 g = t[col[b]];
@@ -1576,10 +1593,14 @@ __global__ __launch_bounds__(GATHER_BLOCK) __attribute__((amdgpu_waves_per_eu(4)
                 re += wa * rre;
                 im += wa * rim;
             }
-            acc += re * cr - im * ci;
+            const double val = re * cr - im * ci;
+#pragma unroll
+            for (int u = 0; u < 6; ++u) acc[u] += u == c ? val : 0.0;
         }
-        A.fields[6 * s + c] = acc;
     }
+    if (!live) return;
+#pragma unroll
+    for (int c = 0; c < 6; ++c) A.fields[6 * s + c] = acc[c];
 }
 
 // Interpolation on the doubled grid (2x supersampling, section 3.4; SS bit 0: z, bit 1: rho), one thread
