@@ -190,6 +190,7 @@ struct DepositArgs {
     double shift;           // shift of the sample positions along z (charge density; J_z of the in-graph
                             // sample current)
     int rho_xy;             // moving samples: also deposit the planar density differential into plane 3
+    int per_block;          // moving samples: samples per block (set by the launch)
     void *j[kMaxBatch];     // the problems' current (3 planes; J_z is plane 2), or charge density (1 plane)
 };
 hipError_t launch_deposit_jz(int prec, const DepositArgs &a, hipStream_t s);

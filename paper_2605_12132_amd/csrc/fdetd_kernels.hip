@@ -775,166 +775,455 @@ __global__ __launch_bounds__(256) void k_deposit_jz(DepositArgs A)
     }
 }
 
-// Currents of moving samples (section 3.6) and the planar density differential (section 3.7), one thread
-// per sample (z, x, y, q w, v_x, v_y, v_z, unused), positions +- v dt/2:
+// All currents of one sample, added node by node with global atomics: samples that move more than 3 cells in a
+// step, whose shapes do not fit the block's tile.
+template <typename R>
+__device__ __noinline__ void deposit_sample_wide(double eps, bool rho_xy, const ProbDesc *Dp, R *j, const double *q)
+{
+    const ProbDesc &D = *Dp;
+    const double h = 0.5 * D.dt, inv_dt = 1.0 / D.dt, inv_dz = 1.0 / D.dz;
+    const double par_s = fold_mS(D.m), par_a = fold_mA(D.m);
+    const size_t pl = 2 * D.plane;  // one plane in R units (interleaved complex)
+    const double zp = (q[0] + h * q[6]) / D.dz, zm = (q[0] - h * q[6]) / D.dz;
+    const double z = q[0], x = q[1], y = q[2], qw = q[3], vx = q[4], vy = q[5];
+    const double r0 = sqrt(x * x + y * y), zc = z / D.dz;
+    const double vr = r0 > 0.0 ? (x * vx + y * vy) / r0 : 0.0, vt = r0 > 0.0 ? (x * vy - y * vx) / r0 : 0.0;
+    if (vr != 0.0 || vt != 0.0) {  // transverse currents at the sample (m_A fold)
+        const SampleShape S0 = sample_shape(D, r0, x, y, eps, par_a);
+        const int lo = (int)floor(zc) - 1;
+        for (int jr = 0; jr < 7; ++jr) {
+            const int k = S0.kc - 3 + jr;
+            for (int u = 0; u < 4; ++u) {
+                const double w = qw * bspline3(lo + u - zc) * inv_dz * S0.w[jr];
+                if (w == 0.0) continue;
+                R *c = j + 2 * ((size_t)k * D.nz + lo + u);
+                atomicAdd(c, (R)(w * vr * S0.ar));
+                atomicAdd(c + 1, (R)(w * vr * S0.ai));
+                atomicAdd(c + pl, (R)(w * vt * S0.ar));
+                atomicAdd(c + pl + 1, (R)(w * vt * S0.ai));
+            }
+        }
+    }
+    const double xp = x + h * vx, yp = y + h * vy, xm = x - h * vx, ym = y - h * vy;
+    const SampleShape Sp = sample_shape(D, sqrt(xp * xp + yp * yp), xp, yp, eps, par_s);
+    const SampleShape Sm = sample_shape(D, sqrt(xm * xm + ym * ym), xm, ym, eps, par_s);
+    deposit_z_wide<R>(j + 2 * pl, rho_xy ? j + 3 * pl : nullptr, D, Sp, Sm, qw, zp, zm,
+                      (int)floor(fmin(zp, zm)) - 1, (int)floor(fmax(zp, zm)) + 2, inv_dt, inv_dz);
+}
+
+// Currents of moving samples (section 3.6) and the planar density differential (section 3.7); samples hold
+// z, x, y, q w, v_x, v_y, v_z, unused, and positions +- v dt/2 give:
 //   J_rho, J_theta += q w v_rho|theta S(z_p) R_A(rho_p) A(theta_p)          (planes 0, 1)
 //   J_z(i - 1/2)   += q w dF(i) (R_S(rho+) A(theta+) + R_S(rho-) A(theta-)) / 2  (plane 2)
 //   rho_xy         += q w (S(z+) + S(z-)) / 2 (R_S(rho+) A(theta+) - R_S(rho-) A(theta-)) / dt  (plane 3)
-// R_A / R_S: radial shape folded with fold_mA / fold_mS.  Samples whose z shapes leave the grid are
-// skipped.
-// As k_deposit_jz, blocks of DEP_PER_THREAD x 256 consecutive samples accumulate in an LDS tile of
-// DEP_TILE_CUR cells (all planes) when their footprint fits.  A sample whose integrated z shape spans more
-// than 8 nodes (it moves more than 3 cells in a step) adds everything with global atomics instead.
-constexpr int DEP_TILE_CUR = 1024;
-template <typename R>
-__global__ __launch_bounds__(256) void k_deposit_current(DepositArgs A)
+// R_A / R_S: radial shape folded with fold_mA / fold_mS (rows below the axis onto row -1 - q, times the sign).
+// Samples whose z shapes leave the grid are skipped.
+//
+// What bounds it is the adds: with a thread per sample the lanes of a wavefront, neighbours in the input, hit
+// the same few nodes, and their atomics serialise (10^6 samples of a bunch into three modes: 945 us, against
+// ~100 us of arithmetic).  But the currents of the samples of one cell are a matrix product over the samples,
+//   O[(row, node)][(component, mode, part)] = sum_s (R[s][row] Z[s][node]) (V[s][component] A[s][mode, part]),
+// so a block takes `per` consecutive samples, and
+//   1. orders them by the cell they lie in (a counting sort in LDS), which makes long runs of one cell;
+//   2. forms each sample's factors R, Z, V A, once for all modes of the grid, one lane per sample, in LDS;
+//   3. sums each run with FP64 matrix instructions, four samples at a time (16 x 16 x 4: the 4 rows x 4 nodes
+//      of a shape against up to 12 columns), and adds the sums of a finished run to the block's LDS tile;
+//   4. adds the tile to the planes, one global atomic per touched value.
+// A block whose samples touch more cells than the tile holds adds the sums of its runs to the planes.  Where runs
+// are short (more than DEPC_RUNS among 64 samples: the ends of a bunch, or samples in no order) each lane adds its
+// own sample instead: a run costs about as much as 64 lanes' samples together, and the sparse end blocks set the
+// kernel's time (without this path 1150 us; DEPC_RUNS 4 / 8 / 12 / 20: 522 / 426 / 408 / 449 us; blocks of 512
+// and 256 samples 510 and 614 us).  10^6 samples of a bunch, three modes of an 8192 x 1024 grid, FP64: 945 -> 408 us.
+constexpr int DEPC_THREADS = 256, DEPC_WAVES = DEPC_THREADS / 64, DEPC_MAX = 1024;  // most samples per block
+constexpr int DEPC_MODES = 3;       // modes per pass: two components of each in 16 columns
+constexpr int DEPC_ROWS = 128;      // rows of the table of radial factors
+constexpr int DEPC_BINS = 8192;     // most bins of the sort
+constexpr int DEPC_RUNS = 12;       // more runs among 64 samples: a lane per sample (short runs do not repay step 3)
+constexpr int DEPC_LDS = 163840 - 2048 - DEPC_ROWS * 16 - 256;  // what records and tile share (160 KiB per CU)
+// record: radial weights at the sample, at +, at - (4 each), z weights (4), integrated z weights (8), then the
+// columns of the products: the angular factors times v_rho, times v_theta (6 each), those at + and at - (6 each);
+// with rho_xy the mean z weights (8).  An odd number of doubles: the lanes that write records hit distinct banks.
+enum { RC_R0 = 0, RC_RP = 4, RC_RM = 8, RC_WZ = 12, RC_DF = 16, RC_CA = 24, RC_AP = 36, RC_AM = 42, RC_SZ = 48 };
+typedef double v4d __attribute__((ext_vector_type(4)));
+template <typename R, bool RXY>
+__global__ __launch_bounds__(DEPC_THREADS) void k_deposit_current(DepositArgs A)
 {
-    __shared__ double tile[2 * 4 * DEP_TILE_CUR];
-    __shared__ int red[16];
-    const int64_t s0 = ((int64_t)blockIdx.x * 256 + threadIdx.x) * DEP_PER_THREAD;
-    const int npl = A.rho_xy ? 4 : 3;
-    for (int p = 0; p < A.nprob; ++p) {
-        const ProbDesc &D = A.probs[p];
-        const double h = 0.5 * D.dt;
-        auto sample = [&](int u) { const int64_t s = s0 + u; return A.samples + 8 * (s < A.n ? s : 0); };
-        auto on_grid = [&](int u, double &zp, double &zm) {
-            const double *q = sample(u);
-            zp = (q[0] + h * q[6]) / D.dz;
-            zm = (q[0] - h * q[6]) / D.dz;
-            return s0 + u < A.n && z_on_grid(D, zp) && z_on_grid(D, zm);
-        };
-        auto is_wide = [&](double zp, double zm) {
-            return (int)floor(fmax(zp, zm)) + 2 - ((int)floor(fmin(zp, zm)) - 1) + 1 > 8;
-        };
-        auto rows_of = [&](double r, int &k0, int &k1) {
-            const int kc = (int)floor(r / D.dr);
-            k0 = kc - 3 > 0 ? kc - 3 : 0;
-            k1 = kc + 3 < D.nr - 1 ? kc + 3 : D.nr - 1;
-        };
-        int fp[4] = {INT_MAX, INT_MIN, INT_MAX, INT_MIN};  // zmin, zmax, kmin, kmax
+    constexpr int NPL = RXY ? 4 : 3, NG = DEPC_MODES, REC = RXY ? 57 : 49;
+    constexpr int TILE = (DEPC_LDS - DEPC_WAVES * 64 * REC * 8) / 8 & ~1, MAX_CELLS = TILE / (2 * NPL);
+    __shared__ double tile[TILE];
+    __shared__ double rec[DEPC_WAVES][64][REC];
+    __shared__ double2 rtab[DEPC_ROWS];  // rho_k^(eps-1), and the row's weight in the normalisation
+    __shared__ unsigned short order[DEPC_MAX];
+    __shared__ int red[4 * DEPC_WAVES + 1];
+    int *bins = (int *)&rec[0][0][0];  // the sort is over before records are written
+    static_assert(sizeof(rec) >= DEPC_BINS * sizeof(int), "bins of the sort");
+    const int per = A.per_block, lane = threadIdx.x % 64, wv = threadIdx.x / 64;
+    // blocks from both ends of the input inwards: the sparse ends of a bunch in position order, whose runs are
+    // short, start first
+    const unsigned bi = blockIdx.x & 1 ? gridDim.x - 1 - blockIdx.x / 2 : blockIdx.x / 2;
+    const int64_t s0 = (int64_t)bi * per;
+    const int ns = (int)(A.n - s0 < per ? A.n - s0 : per);
+    constexpr int UT = DEPC_MAX / DEPC_THREADS;
+    for (int p0 = 0; p0 < A.nprob;) {
+        const ProbDesc &D = A.probs[p0];
+        int same = 1;  // problems from p0 on that are modes of one grid
+        while (p0 + same < A.nprob && A.probs[p0 + same].nz == D.nz && A.probs[p0 + same].nr == D.nr &&
+               A.probs[p0 + same].dz == D.dz && A.probs[p0 + same].dr == D.dr && A.probs[p0 + same].dt == D.dt)
+            ++same;
+        const double h = 0.5 * D.dt, dz = D.dz, dr = D.dr;
+        const int nz = D.nz, nr = D.nr;
+        const size_t plane = D.plane;
+        auto base_row = [&](double rc) { return (int)floor(rc - 0.5) - 1; };  // rows b .. b + 3, rc = rho / dr
+        // footprint of the block's samples
+        int fp[4] = {INT_MAX, INT_MIN, INT_MAX, INT_MIN};  // zmin, zmax, kmin, kmax (kmax not clipped to the grid)
+        int cz[UT], cr_[UT];
 #pragma unroll
-        for (int u = 0; u < DEP_PER_THREAD; ++u) {
-            double zp, zm;
-            if (!on_grid(u, zp, zm) || is_wide(zp, zm)) continue;
-            const double *q = sample(u);
-            fp[0] = min(fp[0], (int)floor(fmin(zp, zm)) - 1);
-            fp[1] = max(fp[1], (int)floor(fmax(zp, zm)) + 2);
+        for (int u = 0; u < UT; ++u) {
+            const int i = threadIdx.x + u * DEPC_THREADS;
+            cz[u] = INT_MIN;
+            cr_[u] = 0;
+            if (i >= ns) continue;
+            const double *q = A.samples + 8 * (s0 + i);
+            const double zp = (q[0] + h * q[6]) / dz, zm = (q[0] - h * q[6]) / dz;
+            if (!z_on_grid(D, zp) || !z_on_grid(D, zm)) continue;
+            const int lo = (int)floor(fmin(zp, zm)) - 1, hi = (int)floor(fmax(zp, zm)) + 2;
+            if (hi - lo + 1 > 8) {
+                for (int p = p0; p < p0 + same; ++p) deposit_sample_wide<R>(A.eps, RXY, A.probs + p, (R *)A.j[p], q);
+                continue;
+            }
+            cz[u] = 2 * lo + ((int)floor(q[0] / dz) - 1 > lo ? 1 : 0);  // nodes of the J_z shape, then of the sample's
+            fp[0] = min(fp[0], lo);
+            fp[1] = max(fp[1], hi);
             const double xs[3] = {q[1], q[1] + h * q[4], q[1] - h * q[4]}, ys[3] = {q[2], q[2] + h * q[5], q[2] - h * q[5]};
+#pragma unroll
             for (int c = 0; c < 3; ++c) {
-                int a, b;
-                rows_of(sqrt(xs[c] * xs[c] + ys[c] * ys[c]), a, b);
-                fp[2] = min(fp[2], a);
-                fp[3] = max(fp[3], b);
+                const int b = base_row(fmin(sqrt(xs[c] * xs[c] + ys[c] * ys[c]) / dr, nr + 8.0));
+                if (c == 0) cr_[u] = b;
+                fp[2] = min(fp[2], max(b, 0));
+                fp[3] = max(fp[3], b + 3);
             }
         }
-        block_minmax(fp, red);
-        // fp covers the narrow samples only; without any the tile is empty (wide samples add directly)
-        const int tz = fp[1] >= fp[0] ? fp[1] - fp[0] + 1 : 0, tr = fp[1] >= fp[0] ? fp[3] - fp[2] + 1 : 0;
-        const bool use_tile = tz > 0 && (int64_t)tz * tr <= DEP_TILE_CUR;  // uniform across the block
-        R *j = (R *)A.j[p];
-        const size_t pl = 2 * D.plane;  // one plane in R units (interleaved complex)
-        if (use_tile) {
-            for (int c = threadIdx.x; c < 2 * npl * tz * tr; c += 256) tile[c] = 0.0;
+        block_minmax<DEPC_WAVES>(fp, red);
+        if (fp[1] < fp[0]) {  // nothing (or only wide samples) here
+            p0 += same;
+            continue;
+        }
+        const int kend = min(fp[3], nr - 1), tz = fp[1] - fp[0] + 1, tr = max(kend - fp[2] + 1, 0);
+        const int cells = (int64_t)tz * tr <= MAX_CELLS ? tz * tr : 0;  // 0: no tile
+        // counting sort by nodes and row (base rows from fp[2] - 2 on); with too many bins the samples stay in order
+        const int br = fp[3] - fp[2] + 3;
+        const bool sorted = (int64_t)2 * tz * br <= DEPC_BINS;
+        const int nbins = sorted ? 2 * tz * br : 0;
+        if (sorted) {
+            for (int c = threadIdx.x; c < nbins; c += DEPC_THREADS) bins[c] = 0;
             __syncthreads();
-        }
-        const double inv_dt = 1.0 / D.dt, inv_dz = 1.0 / D.dz;
-        const double par_s = fold_mS(D.m), par_a = fold_mA(D.m);
-        bool tiled = use_tile;  // false for a wide sample
-        auto add = [&](int plane, int k, int i, double re, double im) {
-            if (tiled) {
-                double *c = tile + 2 * ((plane * tr + k - fp[2]) * tz + i - fp[0]);
-                atomicAdd(c, re);
-                atomicAdd(c + 1, im);
-            } else {
-                R *c = j + plane * pl + 2 * ((size_t)k * D.nz + i);
-                atomicAdd(c, (R)re);
-                atomicAdd(c + 1, (R)im);
+            int bin[UT], rank[UT];
+#pragma unroll
+            for (int u = 0; u < UT; ++u) {
+                bin[u] = -1;
+                if (cz[u] == INT_MIN) continue;
+                bin[u] = min(max(cz[u] - 2 * fp[0], 0), 2 * tz - 1) * br + min(max(cr_[u] - fp[2] + 2, 0), br - 1);
+                rank[u] = atomicAdd(&bins[bin[u]], 1);
             }
+            __syncthreads();
+            // exclusive sums of the bins: each thread its run of bins, then across threads
+            const int run = (nbins + DEPC_THREADS - 1) / DEPC_THREADS, c0 = threadIdx.x * run, c1 = min(c0 + run, nbins);
+            int sum = 0;
+            for (int c = c0; c < c1; ++c) sum += bins[c];
+            int inc = sum;
+            for (int o = 1; o < 64; o <<= 1) {
+                const int t = __shfl_up(inc, o);
+                if (lane >= o) inc += t;
+            }
+            if (lane == 63) red[wv] = inc;
+            __syncthreads();
+            int start = inc - sum;
+            for (int w = 0; w < wv; ++w) start += red[w];
+            for (int c = c0; c < c1; ++c) {
+                const int v = bins[c];
+                bins[c] = start;
+                start += v;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < UT; ++u)
+                if (bin[u] >= 0) order[bins[bin[u]] + rank[u]] = (unsigned short)(threadIdx.x + u * DEPC_THREADS);
+            if (threadIdx.x == 0) {
+                int total = 0;
+                for (int w = 0; w < DEPC_WAVES; ++w) total += red[w];
+                red[4 * DEPC_WAVES] = total;
+            }
+        } else {
+            for (int i = threadIdx.x; i < ns; i += DEPC_THREADS) order[i] = (unsigned short)i;
+            if (threadIdx.x == 0) red[4 * DEPC_WAVES] = ns;
+        }
+        // radial factors of the rows
+        const int rows = min(fp[3] - fp[2] + 1, DEPC_ROWS), t0 = fp[2];
+        auto row_factor = [&](int k) {
+            const double rk = (k + 0.5) * dr, t = rk_pow(rk, A.eps - 1.0);
+            return double2{t, (k == 0 ? 7.0 / 8.0 : (k == 1 ? 73.0 / 72.0 : 1.0)) * (rk * t) * dr};
         };
+        for (int c = threadIdx.x; c < rows; c += DEPC_THREADS) rtab[c] = row_factor(t0 + c);
+        __syncthreads();
+        const int total = red[4 * DEPC_WAVES];
+        const int share = (total + DEPC_WAVES - 1) / DEPC_WAVES;  // samples per wavefront
+        const int w0 = min(wv * share, total), w1 = min(w0 + share, total);
+        const int gfit = cells > 0 ? min(NG, TILE / (2 * NPL * cells)) : NG;
+        for (int g0 = 0; g0 < same; g0 += gfit) {
+            const int ng = min(gfit, same - g0);
+            const int vals = 2 * NPL * cells;  // tile doubles of a mode
+            for (int c = threadIdx.x; c < ng * vals; c += DEPC_THREADS) tile[c] = 0.0;
+            __syncthreads();
+            // The operands' lanes: A (row, node) = (lane / 4 % 4, lane % 4), B column lane % 16, both of sample
+            // lane / 16 of the four; the sums come back as column lane % 16, node lane / 16, row r in element r.
+            const int arow = lane >> 2 & 3, anode = lane & 3, ks = lane >> 4, col = lane & 15;
+            const int ca = min(col, 11), cj = min(col, 5), node = lane >> 4;
+            // this lane's column: component (of the transverse product), mode, part
+            const int comp = ca / 6, g_a = ca % 6 / 2, g_j = cj / 2, part = col & 1;
+            const int m_a = A.probs[p0 + g0 + min(g_a, ng - 1)].m, m_j = A.probs[p0 + g0 + min(g_j, ng - 1)].m;
+            R *const j_a = (R *)A.j[p0 + g0 + min(g_a, ng - 1)], *const j_j = (R *)A.j[p0 + g0 + min(g_j, ng - 1)];
+            const bool on_a = col < 12 && g_a < ng && (m_a != 0 || part == 0), on_j = col < 6 && g_j < ng && (m_j != 0 || part == 0);
+            // adds the sums d[r] of rows b + r at node i; the rows below the axis are first folded onto rows -1 - q
+            // (opposite parts of a sample on the axis then cancel exactly)
+            auto add = [&](bool on, int pl, int g, R *jp, double fold, int b, int i, v4d d) {
+                if (b == -1) d[1] += fold * d[0];
+                if (b == -2) {
+                    d[3] += fold * d[0];
+                    d[2] += fold * d[1];
+                }
+                if (!on || i < 0 || i >= nz) return;
+                const bool in_z = cells > 0 && i >= fp[0] && i <= fp[1];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int k = b + r;
+                    if (k < 0 || k >= nr || d[r] == 0.0) continue;
+                    if (in_z && k >= fp[2] && k <= kend)
+                        atomicAdd(tile + g * vals + 2 * ((pl * tr + k - fp[2]) * tz + i - fp[0]) + part, d[r]);
+                    else atomicAdd(jp + pl * 2 * plane + 2 * ((size_t)k * nz + i) + part, (R)d[r]);
+                }
+            };
+            const v4d vzero = {0.0, 0.0, 0.0, 0.0};
+            v4d dA = vzero, dP0 = vzero, dP1 = vzero, dM0 = vzero, dM1 = vzero, dX0 = vzero, dX1 = vzero, dY0 = vzero, dY1 = vzero;
+            int4 cur{INT_MIN, 0, 0, 0};  // the run's cell: first node, base row, offset of base rows + and -, first node of J_z
+            auto flush = [&]() {
+                if (cur.x == INT_MIN) return;
+                const int bp = cur.y + (cur.z >> 16), bm = bp + (int)(short)(cur.z & 0xffff);
+                add(on_a, comp, g_a, j_a, fold_mA(m_a), cur.y, cur.x + node, dA);
+                const double fs = fold_mS(m_j);
+                if (bp == bm) {  // both positions in the same rows
+                    add(on_j, 2, g_j, j_j, fs, bp, cur.w + node, dP0 + dM0);
+                    add(on_j, 2, g_j, j_j, fs, bp, cur.w + 4 + node, dP1 + dM1);
+                } else {
+                    add(on_j, 2, g_j, j_j, fs, bp, cur.w + node, dP0);
+                    add(on_j, 2, g_j, j_j, fs, bp, cur.w + 4 + node, dP1);
+                    add(on_j, 2, g_j, j_j, fs, bm, cur.w + node, dM0);
+                    add(on_j, 2, g_j, j_j, fs, bm, cur.w + 4 + node, dM1);
+                }
+                if constexpr (RXY) {
+                    add(on_j, 3, g_j, j_j, fs, bp, cur.w + node, dX0);
+                    add(on_j, 3, g_j, j_j, fs, bp, cur.w + 4 + node, dX1);
+                    add(on_j, 3, g_j, j_j, fs, bm, cur.w + node, -dY0);
+                    add(on_j, 3, g_j, j_j, fs, bm, cur.w + 4 + node, -dY1);
+                }
+            };
+            for (int c0 = w0; c0 < w1; c0 += 64) {
+                const int nc = min(64, w1 - c0);
+                int4 key{INT_MIN, 0, 0, 0};
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                if (lane < nc) {
+                    double *r = rec[wv][lane];
+                    const double *q = A.samples + 8 * (s0 + order[c0 + lane]);
+                    const double z = q[0], x = q[1], y = q[2], qw = q[3], vx = q[4], vy = q[5], vz = q[6];
+                    const double zc = z / dz, zp = (z + h * vz) / dz, zm = (z - h * vz) / dz;
+                    const int lo = (int)floor(zc) - 1, l2 = (int)floor(fmin(zp, zm)) - 1, h2 = (int)floor(fmax(zp, zm)) + 2;
+                    const bool ok = z_on_grid(D, zp) && z_on_grid(D, zm) && h2 - l2 + 1 <= 8;
+                    int b[3] = {0, 0, 0};
+                    double cs[3], sn[3], vel[2] = {0.0, 0.0};
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) {
+                        const double sg = c == 0 ? 0.0 : (c == 1 ? h : -h), xx = x + sg * vx, yy = y + sg * vy;
+                        const double rho = sqrt(xx * xx + yy * yy), rc = rho / dr;
+                        b[c] = base_row(fmin(rc, nr + 8.0));
+                        double w[4], N = 0.0;
+#pragma unroll
+                        for (int jj = 0; jj < 4; ++jj) {
+                            const int qq = b[c] + jj, k = qq < 0 ? -1 - qq : qq;
+                            const double2 t = k - t0 >= 0 && k - t0 < rows ? rtab[k - t0] : row_factor(k);
+                            const double bs = bspline3(qq + 0.5 - rc);
+                            N += t.y * bs;
+                            w[jj] = t.x * bs;
+                        }
+                        const double inv = N != 0.0 ? (c == 0 ? 1.0 : 0.5) / N : 0.0;
+#pragma unroll
+                        for (int jj = 0; jj < 4; ++jj) r[4 * c + jj] = w[jj] * inv;  // R0, R+ / 2, R- / 2
+                        cs[c] = rho > 0.0 ? xx / rho : 1.0;
+                        sn[c] = rho > 0.0 ? yy / rho : 0.0;
+                        if (c == 0 && rho > 0.0) {
+                            vel[0] = cs[0] * vx + sn[0] * vy;
+                            vel[1] = cs[0] * vy - sn[0] * vx;
+                        }
+                    }
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) r[RC_WZ + v] = qw * bspline3(lo + v - zc) / dz;
+                    double Fp = 0.0, Fm = 0.0;
+#pragma unroll
+                    for (int v = 0; v < 8; ++v) {
+                        double df = 0.0, sz = 0.0;
+                        if (l2 + v <= h2) {
+                            df = qw * ((Fm - Fp) / D.dt);
+                            const double bp = bspline3(l2 + v - zp), bm = bspline3(l2 + v - zm);
+                            Fp += bp;
+                            Fm += bm;
+                            if constexpr (RXY) sz = qw * (bp + bm) / dz / D.dt;  // times R+- / 2
+                        }
+                        r[RC_DF + v] = df;
+                        if constexpr (RXY) r[RC_SZ + v] = sz;
+                    }
+#pragma unroll
+                    for (int g = 0; g < NG; ++g) {
+                        const int m = A.probs[p0 + g0 + min(g, ng - 1)].m;
+#pragma unroll
+                        for (int c = 0; c < 3; ++c) {
+                            double ar = 0.5 / M_PI, ai = 0.0;
+                            if (m) {
+                                double a = 1.0, bb = 0.0;
+                                for (int u = 0; u < m; ++u) {
+                                    const double t = a * cs[c] - bb * sn[c];
+                                    bb = a * sn[c] + bb * cs[c];
+                                    a = t;
+                                }
+                                ar = a / M_PI;
+                                ai = -bb / M_PI;
+                            }
+                            if (c == 0) {
+                                r[RC_CA + 2 * g] = vel[0] * ar;
+                                r[RC_CA + 2 * g + 1] = vel[0] * ai;
+                                r[RC_CA + 6 + 2 * g] = vel[1] * ar;
+                                r[RC_CA + 6 + 2 * g + 1] = vel[1] * ai;
+                            } else {
+                                r[(c == 1 ? RC_AP : RC_AM) + 2 * g] = ar;
+                                r[(c == 1 ? RC_AP : RC_AM) + 2 * g + 1] = ai;
+                            }
+                        }
+                    }
+                    // (row offsets of + and - as 16-bit numbers: they are clamped to the grid's rows + 8)
+                    const int dp = b[1] - b[0], dm = b[2] - b[1];
+                    const bool near = dp > -32768 && dp < 32768 && dm > -32768 && dm < 32768;
+                    if (ok && near) key = int4{lo, b[0], (int)((unsigned)dp << 16 | ((unsigned)dm & 0xffffu)), l2};
+                    else if (ok)
+                        for (int g = 0; g < ng; ++g) deposit_sample_wide<R>(A.eps, RXY, A.probs + p0 + g0 + g, (R *)A.j[p0 + g0 + g], q);
+                }
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                // runs of equal cells among the chunk's samples
+                const int px = __shfl_up(key.x, 1), py = __shfl_up(key.y, 1), pz = __shfl_up(key.z, 1), pw = __shfl_up(key.w, 1);
+                unsigned long long starts = __ballot(lane < nc && (lane == 0 || key.x != px || key.y != py || key.z != pz || key.w != pw));
+                if (__popcll(starts) > DEPC_RUNS) {
+                    // many short runs: every lane adds its own sample, node by node
+                    if (lane < nc && key.x != INT_MIN) {
+                        const double *r = rec[wv][lane];
+                        const int bp = key.y + (key.z >> 16), bm = bp + (int)(short)(key.z & 0xffff);
 #pragma unroll 1
-        for (int u = 0; u < DEP_PER_THREAD; ++u) {
-            double zp, zm;
-            if (!on_grid(u, zp, zm)) continue;
-            const bool wide = is_wide(zp, zm);
-            tiled = use_tile && !wide;
-            const double *q = sample(u);
-            const double z = q[0], x = q[1], y = q[2], qw = q[3], vx = q[4], vy = q[5];
-            const double r0 = sqrt(x * x + y * y), zc = z / D.dz;
-            const double vr = r0 > 0.0 ? (x * vx + y * vy) / r0 : 0.0, vt = r0 > 0.0 ? (x * vy - y * vx) / r0 : 0.0;
-            const double xp = x + h * vx, yp = y + h * vy, xm = x - h * vx, ym = y - h * vy;
-            const double rp = sqrt(xp * xp + yp * yp), rm = sqrt(xm * xm + ym * ym);
-            // transverse currents at the sample (m_A fold)
-            if (vr != 0.0 || vt != 0.0) {
-                const SampleShape S0 = sample_shape(D, r0, x, y, A.eps, par_a);
-                const int lo = (int)floor(zc) - 1;
-                double wz[4];
-#pragma unroll
-                for (int u2 = 0; u2 < 4; ++u2) wz[u2] = qw * bspline3(lo + u2 - zc) * inv_dz;
-#pragma unroll
-                for (int jr = 0; jr < 7; ++jr) {
-                    const int k = S0.kc - 3 + jr;
-                    const double rs = S0.w[jr];
-                    if (rs == 0.0) continue;
-                    for (int u2 = 0; u2 < 4; ++u2) {
-                        const double w = wz[u2] * rs;
-                        if (w == 0.0) continue;
-                        add(0, k, lo + u2, w * vr * S0.ar, w * vr * S0.ai);
-                        add(1, k, lo + u2, w * vt * S0.ar, w * vt * S0.ai);
+                        for (int g = 0; g < ng; ++g) {
+                            const int m = A.probs[p0 + g0 + g].m;
+                            R *const jp = (R *)A.j[p0 + g0 + g];
+                            auto put = [&](int pl, int k, int i, double re, double im) {
+                                if (k < 0 || k >= nr || (re == 0.0 && im == 0.0)) return;
+                                if (cells > 0 && i >= fp[0] && i <= fp[1] && k >= fp[2] && k <= kend) {
+                                    double *o = tile + g * vals + 2 * ((pl * tr + k - fp[2]) * tz + i - fp[0]);
+                                    atomicAdd(o, re);
+                                    if (m) atomicAdd(o + 1, im);
+                                } else {
+                                    R *o = jp + pl * 2 * plane + 2 * ((size_t)k * nz + i);
+                                    atomicAdd(o, (R)re);
+                                    if (m) atomicAdd(o + 1, (R)im);
+                                }
+                            };
+                            // weight of row b + rr with the row below the axis that folds onto it
+                            auto weight = [&](int base, int b, int rr, double fold) {
+                                const int mirror = -1 - 2 * b - rr;
+                                const double w = r[base + rr];
+                                return mirror >= 0 && mirror < 4 && b + mirror < 0 ? w + fold * r[base + mirror] : w;
+                            };
+                            const double fa = fold_mA(m), fs = fold_mS(m);
+                            const double *c = r + RC_CA + 2 * g;
+#pragma unroll 1
+                            for (int rr = 0; rr < 4; ++rr) {
+                                const double w = weight(RC_R0, key.y, rr, fa);
+                                const double wp = weight(RC_RP, bp, rr, fs), wm = weight(RC_RM, bm, rr, fs);
+                                for (int v = 0; v < 4; ++v) {
+                                    const double t = w * r[RC_WZ + v];
+                                    put(0, key.y + rr, key.x + v, t * c[0], t * c[1]);
+                                    put(1, key.y + rr, key.x + v, t * c[6], t * c[7]);
+                                }
+                                const double pr = wp * r[RC_AP + 2 * g], pi = wp * r[RC_AP + 2 * g + 1];
+                                const double mr = wm * r[RC_AM + 2 * g], mi = wm * r[RC_AM + 2 * g + 1];
+                                for (int v = 0; v < 8; ++v) {
+                                    const double f = r[RC_DF + v];
+                                    if (bp == bm) {
+                                        put(2, bp + rr, key.w + v, f * (pr + mr), f * (pi + mi));
+                                    } else {
+                                        put(2, bp + rr, key.w + v, f * pr, f * pi);
+                                        put(2, bm + rr, key.w + v, f * mr, f * mi);
+                                    }
+                                    if constexpr (RXY) {
+                                        const double sz = r[RC_SZ + v];
+                                        put(3, bp + rr, key.w + v, sz * pr, sz * pi);
+                                        put(3, bm + rr, key.w + v, -sz * mr, -sz * mi);
+                                    }
+                                }
+                            }
+                        }
+                    }
+                    starts = 0;
+                }
+                while (starts) {
+                    const int i0 = __ffsll((long long)starts) - 1;
+                    starts &= starts - 1;
+                    const int i1 = starts ? __ffsll((long long)starts) - 1 : nc;
+                    const int4 k{__shfl(key.x, i0), __shfl(key.y, i0), __shfl(key.z, i0), __shfl(key.w, i0)};
+                    if (k.x != cur.x || k.y != cur.y || k.z != cur.z || k.w != cur.w) {
+                        flush();
+                        cur = k;
+                        dA = dP0 = dP1 = dM0 = dM1 = dX0 = dX1 = dY0 = dY1 = vzero;
+                    }
+                    if (k.x == INT_MIN) continue;
+                    for (int i = i0; i < i1; i += 4) {
+                        // samples past the run's end enter as zeros
+                        const bool in = i + ks < i1;
+                        const double *r = rec[wv][in ? i + ks : i];
+                        const double a0 = r[RC_R0 + arow] * r[RC_WZ + anode], b0 = r[RC_CA + ca];
+                        const double rp = r[RC_RP + arow], rm = r[RC_RM + arow], f0 = r[RC_DF + anode], f1 = r[RC_DF + 4 + anode];
+                        const double bp = r[RC_AP + cj], bm = r[RC_AM + cj];
+                        auto z0 = [&](double v) { return in ? v : 0.0; };
+                        dA = __builtin_amdgcn_mfma_f64_16x16x4f64(z0(a0), z0(b0), dA, 0, 0, 0);
+                        dP0 = __builtin_amdgcn_mfma_f64_16x16x4f64(z0(rp * f0), z0(bp), dP0, 0, 0, 0);
+                        dP1 = __builtin_amdgcn_mfma_f64_16x16x4f64(z0(rp * f1), z0(bp), dP1, 0, 0, 0);
+                        dM0 = __builtin_amdgcn_mfma_f64_16x16x4f64(z0(rm * f0), z0(bm), dM0, 0, 0, 0);
+                        dM1 = __builtin_amdgcn_mfma_f64_16x16x4f64(z0(rm * f1), z0(bm), dM1, 0, 0, 0);
+                        if constexpr (RXY) {
+                            const double g0_ = r[RC_SZ + anode], g1_ = r[RC_SZ + 4 + anode];
+                            dX0 = __builtin_amdgcn_mfma_f64_16x16x4f64(z0(rp * g0_), z0(bp), dX0, 0, 0, 0);
+                            dX1 = __builtin_amdgcn_mfma_f64_16x16x4f64(z0(rp * g1_), z0(bp), dX1, 0, 0, 0);
+                            dY0 = __builtin_amdgcn_mfma_f64_16x16x4f64(z0(rm * g0_), z0(bm), dY0, 0, 0, 0);
+                            dY1 = __builtin_amdgcn_mfma_f64_16x16x4f64(z0(rm * g1_), z0(bm), dY1, 0, 0, 0);
+                        }
                     }
                 }
             }
-            // longitudinal current and planar density differential over the nodes of both z shapes
-            const int lo = (int)floor(fmin(zp, zm)) - 1, hi = (int)floor(fmax(zp, zm)) + 2;
-            if (wide) {
-                const SampleShape Sp = sample_shape(D, rp, xp, yp, A.eps, par_s), Sm = sample_shape(D, rm, xm, ym, A.eps, par_s);
-                deposit_z_wide<R>(j + 2 * pl, A.rho_xy ? j + 3 * pl : nullptr, D, Sp, Sm, qw, zp, zm, lo, hi, inv_dt, inv_dz);
-                continue;
-            }
-            double dF[8], sz[8];  // nodes lo .. hi (at most 8), 0 beyond
-            double Fp = 0.0, Fm = 0.0;
-#pragma unroll
-            for (int v = 0; v < 8; ++v) {
-                dF[v] = sz[v] = 0.0;
-                if (v > hi - lo) continue;
-                dF[v] = (Fm - Fp) * inv_dt;
-                const double bp = bspline3(lo + v - zp), bm = bspline3(lo + v - zm);
-                Fp += bp;
-                Fm += bm;
-                sz[v] = 0.5 * (bp + bm) * inv_dz;
-            }
-            // rows of both shapes
-            const SampleShape Sp = sample_shape(D, rp, xp, yp, A.eps, par_s), Sm = sample_shape(D, rm, xm, ym, A.eps, par_s);
-            const int k0 = min(Sp.k0, Sm.k0), k1 = max(Sp.k1, Sm.k1);
-            for (int k = k0; k <= k1; ++k) {
-                const int jp = k - Sp.kc + 3, jm = k - Sm.kc + 3;
-                double wp = 0.0, wm = 0.0;  // selects with static indices keep the shapes in registers
-#pragma unroll
-                for (int q = 0; q < 7; ++q) {
-                    wp = jp == q ? Sp.w[q] : wp;
-                    wm = jm == q ? Sm.w[q] : wm;
-                }
-                if (wp == 0.0 && wm == 0.0) continue;
-                const double sr = 0.5 * (wp * Sp.ar + wm * Sm.ar), si = 0.5 * (wp * Sp.ai + wm * Sm.ai);
-                const double dr_ = (wp * Sp.ar - wm * Sm.ar) * inv_dt, di = (wp * Sp.ai - wm * Sm.ai) * inv_dt;
-#pragma unroll
-                for (int v = 0; v < 8; ++v) {
-                    if (dF[v] != 0.0) add(2, k, lo + v, qw * dF[v] * sr, qw * dF[v] * si);
-                    if (A.rho_xy && sz[v] != 0.0) add(3, k, lo + v, qw * sz[v] * dr_, qw * sz[v] * di);
-                }
-            }
-        }
-        if (use_tile) {
+            flush();
             __syncthreads();
-            for (int c = threadIdx.x; c < npl * tz * tr; c += 256) {
+            for (int c = threadIdx.x; c < ng * NPL * cells; c += DEPC_THREADS) {
                 const double re = tile[2 * c], im = tile[2 * c + 1];
                 if (re == 0.0 && im == 0.0) continue;
-                const int plane = c / (tz * tr), cell = c % (tz * tr);
-                R *g = j + plane * pl + 2 * ((size_t)(fp[2] + cell / tz) * D.nz + fp[0] + cell % tz);
-                atomicAdd(g, (R)re);
-                atomicAdd(g + 1, (R)im);
+                const int g = c / (NPL * cells), pl = c / cells % NPL, cell = c % cells;
+                R *o = (R *)A.j[p0 + g0 + g] + pl * 2 * plane + 2 * ((size_t)(fp[2] + cell / tz) * nz + fp[0] + cell % tz);
+                if (re != 0.0) atomicAdd(o, (R)re);
+                if (im != 0.0) atomicAdd(o + 1, (R)im);
             }
-            __syncthreads();  // the tile is reused by the next problem
+            __syncthreads();  // the tile and the records are used again
         }
+        p0 += same;
     }
 }
 
@@ -1998,13 +2287,21 @@ hipError_t launch_deposit_jz(int prec, const DepositArgs &a, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_deposit_current(int prec, const DepositArgs &a, hipStream_t s)
+hipError_t launch_deposit_current(int prec, const DepositArgs &a0, hipStream_t s)
 {
-    if (a.n <= 0) return hipSuccess;
-    const int64_t per_block = 256 * DEP_PER_THREAD;
-    const dim3 grid((unsigned)((a.n + per_block - 1) / per_block));
-    if (prec == P64) hipLaunchKernelGGL(k_deposit_current<double>, grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL(k_deposit_current<float>, grid, dim3(256), 0, s, a);
+    if (a0.n <= 0) return hipSuccess;
+    DepositArgs a = a0;
+    // samples per block: many make the runs of one cell long, but few samples in all must still fill the chip
+    a.per_block = DEPC_MAX;
+    while (a.per_block > 128 && a.n / a.per_block < 512) a.per_block /= 2;
+    const dim3 grid((unsigned)((a.n + a.per_block - 1) / a.per_block)), block(DEPC_THREADS);
+    if (prec == P64) {
+        if (a.rho_xy) hipLaunchKernelGGL((k_deposit_current<double, true>), grid, block, 0, s, a);
+        else hipLaunchKernelGGL((k_deposit_current<double, false>), grid, block, 0, s, a);
+    } else {
+        if (a.rho_xy) hipLaunchKernelGGL((k_deposit_current<float, true>), grid, block, 0, s, a);
+        else hipLaunchKernelGGL((k_deposit_current<float, false>), grid, block, 0, s, a);
+    }
     return hipGetLastError();
 }
 
