@@ -39,7 +39,7 @@ METRIC = "field cell-updates/s (cells×modes×steps/s), FP64 vs FP32-comp at fix
 # counted; reported only while both still match (the kernel code, and the tiling the timed plan runs).
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_maxwell_stage_lwfa_m012_8192x1024_o32_pmc.md")
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2605_12132_amd", "csrc", f)
-                  for f in ("fdetd_march.hip", "fdetd_tiles.h", "fdetd_internal.h")]
+                  for f in ("fdetd_march.hip", "fdetd_lanes.h", "fdetd_tiles.h", "fdetd_internal.h")]
 N_SAMPLES = 10 ** 6
 
 

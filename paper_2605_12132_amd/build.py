@@ -24,8 +24,8 @@ SOURCES = ([("fdetd_march.hip", f"fdetd_march_nd{lo}_{hi}", [f"-DFDETD_ND_LO={lo
             for lo, hi in ND_RANGES]
            + [("fdetd_march.hip", f"fdetd_march_any{a}", ["-DFDETD_ND_LO=1", "-DFDETD_ND_HI=0", f"-DFDETD_ANY_WIDTH={a}"])
               for a in (0, 1, 2)]  # launches that mix stencil widths: FP64, FP32, FP32 compensated last stage
-           + [(f, f, []) for f in ("fdetd_kernels.hip", "fdetd_noalloc.hip", "fdetd_plan.cpp", "fdetd_coeffs.cpp",
-                                   "fdetd_dispatch.cpp")])
+           + [(f, f, []) for f in ("fdetd_kernels.hip", "fdetd_envelope.hip", "fdetd_noalloc.hip", "fdetd_plan.cpp",
+                                   "fdetd_coeffs.cpp", "fdetd_dispatch.cpp")])
 ARCH = "gfx950"
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden", "-Wall", "-Wno-unused-function",
           "-I", os.path.join(ROOT, "include"), "-I", CSRC]

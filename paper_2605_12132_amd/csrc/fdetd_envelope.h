@@ -1,0 +1,55 @@
+// Fused FP64 envelope stages: when a plan takes them, their tiles and their launch.
+#pragma once
+
+#include "fdetd_internal.h"
+
+#if defined(__HIPCC__)
+#define FDETD_ENV_HD __host__ __device__
+#else
+#define FDETD_ENV_HD
+#endif
+
+namespace fdetd {
+
+// Blocks of kEnvWaves wavefronts side by side along z run env_depth consecutive stages in one pass.  Depth 4 only
+// at N_D = 1: the windows and delay lines of the stages stand in registers, and 4 stages at N_D = 2 already take
+// the 256 of two wavefronts per SIMD (order 4, 4096 x 512: 89 us per 4 stages with depth 2, 106 with depth 4).
+// From N_D = 5 on the march stage by stage is the faster one (order 12, 4096 x 512: 152 us per 4 stages, 171 fused;
+// order 16: 161, 257): the rows that a block forms for its neighbours grow with N_D while the bytes saved do not.
+// FP64 only, where the groups give the same bits as the single stages: the FP32C rows next to the axis, in FP64
+// arithmetic, would reach (S - 1) N_D rows further.
+constexpr int kEnvWaves = 4;
+constexpr int kEnvBlocks = 512;           // blocks that run at a time: two per CU
+constexpr int kEnvFuseND = 4;
+constexpr size_t kEnvFuseCells = 1 << 20;  // in a launch; 2900 x 360, orders 2, 4, 6, 8: 72, 75, 77, 79 us per 4
+                                           // stages one by one, 41, 57, 60, 71 fused; 2048 x 256, order 8: 49, 53
+constexpr int kEnvRows = 640;  // most rows of a march (output rows, and the rows before and behind them)
+constexpr int env_depth(int nd) { return nd == 1 ? 4 : 2; }
+constexpr int env_out_columns(int nd) { return kEnvWaves * 32 - 2 * (env_depth(nd) - 1) * nd; }
+struct EnvFuseArgs {
+    const ProbDesc *probs;
+    int nprob, ntiles;
+    int seg;                       // rows per segment
+    int sel_in, sel_psi, sel_out;  // vectors of the group: 0 the caller's planes, 1, 2 the plan's stage vectors
+    double coef[4];                // of the group's stages, in order
+    int begin[kMaxBatch];          // first tile of each problem
+    const void *a[kMaxBatch], *at[kMaxBatch], *chi[kMaxBatch];
+};
+hipError_t launch_envelope_fused(int nd, const EnvFuseArgs &a, hipStream_t s);
+
+// A tile: first output column, output rows.  Tile r of an nz x nr grid: oc output columns per tile, seg rows per
+// segment, strips numbered fastest.
+struct FuseTile {
+    int o0, k0, k1;
+};
+FDETD_ENV_HD inline int fused_tiles(int nz, int nr, int seg, int oc) { return (nz + oc - 1) / oc * ((nr + seg - 1) / seg); }
+FDETD_ENV_HD inline bool decode_fused(int nz, int nr, int r, int seg, int oc, FuseTile &c)
+{
+    const int ns = (nz + oc - 1) / oc, sl = r / ns;
+    c.o0 = (r - sl * ns) * oc;
+    c.k0 = sl * seg;
+    c.k1 = c.k0 + seg < nr ? c.k0 + seg : nr;
+    return r >= 0 && c.o0 < nz && c.k0 < c.k1;
+}
+
+}  // namespace fdetd

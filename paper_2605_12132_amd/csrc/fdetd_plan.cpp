@@ -22,6 +22,7 @@
 #include <vector>
 
 #include "../../include/fdetd.h"
+#include "fdetd_envelope.h"
 #include "fdetd_internal.h"
 #include "fdetd_tiles.h"
 
@@ -62,6 +63,8 @@ struct Batch {
     int seg;                   // rows per marching segment of the main launch
     int nt_store = 0;          // Maxwell stage outputs stored non-temporal (autotuned)
     int tile_order = 0;        // numbering of the Maxwell tiles (ProbDesc::tile_order, autotuned)
+    int fused = 0;             // envelope: tiles of the fused launch (0: stage by stage)
+    int fused_seg = 0;         // ... and their rows
     int lane = 0;              // stream of the batch's launches: 0 = the plan's stream, l > 0 = lanes[l - 1]
     double dt;
     std::vector<int> members;  // user indices, in table order
@@ -389,16 +392,17 @@ int enqueue_maxwell_batch(fdetd_plan_t P, const Batch &b, void *const *psi, cons
     return FDETD_OK;
 }
 
-// exp(-sigma dt/4) on the absorbing layers of the problems of batch b that have one.
-int damp_layers(fdetd_plan_t P, const Batch &b, void *const *a, void *const *at, hipStream_t s)
+// exp(-sigma dt/4) on the absorbing layers of the problems of batch b that have one.  moved: the state stands in
+// the plan's second stage vector.
+int damp_layers(fdetd_plan_t P, const Batch &b, void *const *a, void *const *at, bool moved, hipStream_t s)
 {
     for (int t = 0; t < b.count; ++t) {
         const int p = b.members[t];
         const Prob &q = P->probs[p];
         if (q.lz == 0 && q.lr == 0) continue;
         DampArgs X{};
-        X.a = a[p];
-        X.at = at[p];
+        X.a = moved ? q.buf[1] : a[p];
+        X.at = moved ? (void *)((char *)q.buf[1] + q.cells * elem_bytes(P->precision)) : at[p];
         X.lo = q.lo;
         X.sz = q.sz;
         X.sr = q.sr;
@@ -412,12 +416,9 @@ int damp_layers(fdetd_plan_t P, const Batch &b, void *const *a, void *const *at,
     return FDETD_OK;
 }
 
-// One envelope step of the problems of batch b on stream s.
-int enqueue_envelope_batch(fdetd_plan_t P, const Batch &b, void *const *a, void *const *at, const void *const *chi,
-                           hipStream_t s)
+// Arguments of batch b's envelope stages; returns the cells of its problems.
+size_t envelope_args(fdetd_plan_t P, const Batch &b, void *const *a, void *const *at, const void *const *chi, BatchArgs &A)
 {
-    const size_t eb = elem_bytes(P->precision);
-    BatchArgs A;
     std::memset(&A, 0, sizeof A);
     A.probs = P->ddesc + b.d0;
     A.nprob = b.count;
@@ -431,7 +432,35 @@ int enqueue_envelope_batch(fdetd_plan_t P, const Batch &b, void *const *a, void 
         A.chi[t] = chi[b.members[t]];
         cells += P->probs[b.members[t]].cells;
     }
-    int rc = damp_layers(P, b, a, at, s);  // first factor exp(-sigma dt/4) of the split step
+    return cells;
+}
+
+// Stages from, ..., 0 of an envelope step, one launch each.
+int enqueue_envelope_stages(fdetd_plan_t P, const Batch &b, BatchArgs &A, size_t cells, int from, hipStream_t s)
+{
+    const size_t eb = elem_bytes(P->precision);
+    for (int n = from; n >= 0; --n) {
+        A.n = n;
+        A.coef = b.dt / (n + 1);
+        // algorithmic bytes: vin (2c) + psi (2c; the same data in the first stage) + chi + vout (2c)
+        const double cvals = (n == b.N - 1 ? 4.0 : 6.0) + 0.5;
+        const double bytes = cvals * cells * eb + (A.compensated && n == 0 ? 2.0 * 2 * cells * 8 : 0.0);
+        int rc = profile_begin(P, bytes);
+        if (!rc) rc = launch_stage(P, b, A, s);
+        if (!rc) rc = profile_end(P);
+        if (rc) return rc;
+    }
+    return FDETD_OK;
+}
+
+// One envelope step of the problems of batch b on stream s.
+int enqueue_envelope_batch(fdetd_plan_t P, const Batch &b, void *const *a, void *const *at, const void *const *chi,
+                           hipStream_t s)
+{
+    const size_t eb = elem_bytes(P->precision);
+    BatchArgs A;
+    const size_t cells = envelope_args(P, b, a, at, chi, A);
+    int rc = damp_layers(P, b, a, at, false, s);  // first factor exp(-sigma dt/4) of the split step
     if (rc) return rc;
     A.increment = (P->flags & FDETD_PLAN_INCREMENT_FORM) ? 1 : 0;
     if (A.increment && b.ntiles + b.ntiles_ax) {
@@ -447,16 +476,7 @@ int enqueue_envelope_batch(fdetd_plan_t P, const Batch &b, void *const *a, void 
         }
         A.role = 0;
     }
-    for (int n = b.N - 1; n >= 0; --n) {
-        A.n = n;
-        A.coef = b.dt / (n + 1);
-        // algorithmic bytes: vin (2c) + psi (2c; the same data in the first stage) + chi + vout (2c)
-        const double cvals = (n == b.N - 1 ? 4.0 : 6.0) + 0.5;
-        const double bytes = cvals * cells * eb + (A.compensated && n == 0 ? 2.0 * 2 * cells * 8 : 0.0);
-        if ((rc = profile_begin(P, bytes))) return rc;
-        if ((rc = launch_stage(P, b, A, s))) return rc;
-        if ((rc = profile_end(P))) return rc;
-    }
+    if ((rc = enqueue_envelope_stages(P, b, A, cells, b.N - 1, s))) return rc;
     for (int t = 0; t < b.count; ++t) {
         const int p = b.members[t];
         const Prob &q = P->probs[p];
@@ -466,7 +486,67 @@ int enqueue_envelope_batch(fdetd_plan_t P, const Batch &b, void *const *a, void 
             HIPCHK(P, launch_copy((char *)q.buf[0] + plane_b, at[p], plane_b, s));
         }
     }
-    return damp_layers(P, b, a, at, s);  // second factor
+    return damp_layers(P, b, a, at, false, s);  // second factor
+}
+
+// One envelope step of batch b in fused groups of env_depth stages.  Blocks read the state beside their own
+// columns and rows, so a group's output stands elsewhere: the state moves between the caller's planes and the
+// plan's second stage vector from step to step, and intermediate vectors alternate between the first stage vector
+// and the state's next place.  step, n_steps: position in the call; the last step leaves the state with the caller:
+// where it starts there, its last group runs stage by stage, whose last stage works in place, or (a single group)
+// the result is copied back (one-step calls, 2900 x 360 and 6000 x 700, order 8: 79 and 355 us stage by
+// stage, 76 and 280 so).
+int enqueue_envelope_fused(fdetd_plan_t P, const Batch &b, void *const *a, void *const *at, const void *const *chi,
+                           int step, int n_steps, hipStream_t s)
+{
+    const size_t eb = elem_bytes(P->precision);
+    const int depth = env_depth(b.nd), groups = b.N / depth;
+    EnvFuseArgs A{};
+    A.probs = P->ddesc + b.d0;
+    A.nprob = b.count;
+    A.ntiles = b.fused;
+    A.seg = b.fused_seg;
+    size_t cells = 0;
+    for (int t = 0, begin = 0; t < b.count; ++t) {
+        const fdetd_problem_desc &d = P->probs[b.members[t]].d;
+        A.begin[t] = begin;
+        begin += fused_tiles(d.nz, d.nr, A.seg, env_out_columns(b.nd));
+        A.a[t] = a[b.members[t]];
+        A.at[t] = at[b.members[t]];
+        A.chi[t] = chi[b.members[t]];
+        cells += P->probs[b.members[t]].cells;
+    }
+    const bool moved = step & 1;
+    A.sel_psi = moved ? 2 : 0;
+    const int next = moved ? 0 : 2;
+    const bool home = step == n_steps - 1 && !moved, tail = home && groups > 1;
+    int rc = damp_layers(P, b, a, at, moved, s);  // first factor exp(-sigma dt/4) of the split step
+    if (rc) return rc;
+    A.sel_in = A.sel_psi;
+    for (int g = 0; g < groups; ++g) {
+        if (tail && g == groups - 1) {  // its stages read the second stage vector first
+            BatchArgs B;
+            envelope_args(P, b, a, at, chi, B);
+            if ((rc = enqueue_envelope_stages(P, b, B, cells, depth - 1, s))) return rc;
+            break;
+        }
+        A.sel_out = (groups - 1 - g - tail) % 2 ? 1 : next;
+        for (int t = 0; t < depth; ++t) A.coef[t] = b.dt / (b.N - g * depth - t);
+        // algorithmic bytes: vin (2c) + psi (2c; the same data in the first group) + chi + out (2c)
+        if ((rc = profile_begin(P, ((g == 0 ? 4.0 : 6.0) + 0.5) * cells * eb))) return rc;
+        HIPCHK(P, launch_envelope_fused(b.nd, A, s));
+        if ((rc = profile_end(P))) return rc;
+        A.sel_in = A.sel_out;
+    }
+    if (home && !tail)
+        for (int t = 0; t < b.count; ++t) {
+            const int p = b.members[t];
+            const Prob &q = P->probs[p];
+            const size_t plane_b = q.cells * eb;
+            HIPCHK(P, launch_copy(q.buf[1], a[p], plane_b, s));
+            HIPCHK(P, launch_copy((char *)q.buf[1] + plane_b, at[p], plane_b, s));
+        }
+    return damp_layers(P, b, a, at, !moved && step < n_steps - 1, s);  // second factor
 }
 
 // Planes of one current block: J_rho, J_theta, J_z, and with the current correction rho_xy.
@@ -688,6 +768,54 @@ int axis_segment_rows()
     return kSegAxis;
 }
 
+// FDETD_ENV_FUSE = 0 or 1 fixes whether envelope steps run in fused groups of stages; -1: unset.
+int forced_env_fuse()
+{
+    if (const char *e = std::getenv("FDETD_ENV_FUSE"))
+        if ((e[0] == '0' || e[0] == '1') && e[1] == 0) return e[0] - '0';
+    return -1;
+}
+
+// Whether batch b's envelope steps (problems D[0 .. b.count)) run in fused groups of stages, and their tiles.
+int plan_fused(fdetd_plan_t P, Batch &b, const ProbDesc *D)
+{
+    if (P->kind != FDETD_ENVELOPE || P->precision != FDETD_FP64 || b.nd < 1 || b.nd > kEnvFuseND || b.N % env_depth(b.nd))
+        return FDETD_OK;
+    size_t cells = 0;
+    for (int t = 0; t < b.count; ++t) cells += D[t].plane;
+    const int force = forced_env_fuse();
+    if (force == 0 || (force < 0 && cells < kEnvFuseCells)) return FDETD_OK;
+    // rows per segment: a block marches them and the rows before its first one, kEnvBlocks at a time
+    const int lag = (env_depth(b.nd) - 1) * b.nd, oc = env_out_columns(b.nd);
+    double least = 1e300;
+    for (int seg = 8; seg + 3 * lag + 4 <= kEnvRows; ++seg) {
+        int64_t blocks = 0;
+        for (int t = 0; t < b.count; ++t) blocks += fused_tiles(D[t].nz, D[t].nr, seg, oc);
+        const double cost = (double)((blocks + kEnvBlocks - 1) / kEnvBlocks) * (seg + 2 * lag + 4);
+        if (cost < least) {
+            least = cost;
+            b.fused_seg = seg;
+            b.fused = (int)blocks;
+        }
+    }
+    // the tiles cover the rows segment by segment, each from column 0 on without gap or overlap
+    for (int t = 0; t < b.count; ++t) {
+        int row = 0, col = 0;
+        for (int r = 0; r < fused_tiles(D[t].nz, D[t].nr, b.fused_seg, oc); ++r) {
+            FuseTile c;
+            if (!decode_fused(D[t].nz, D[t].nr, r, b.fused_seg, oc, c) || c.k0 != row || c.o0 != col || c.k1 > D[t].nr)
+                return fail(P, FDETD_E_ARG, "internal: fused tile %d of a %dx%d grid", r, D[t].nz, D[t].nr);
+            col += oc;
+            if (col >= D[t].nz) {
+                col = 0;
+                row = c.k1;
+            }
+        }
+        if (col || row != D[t].nr) return fail(P, FDETD_E_ARG, "internal: fused tiles of a %dx%d grid", D[t].nz, D[t].nr);
+    }
+    return FDETD_OK;
+}
+
 // Group problems into launch batches, fill the descriptor table and upload it.  P->seg_rows gives the
 // segment length of each batch; when it does not match the batch count the defaults are taken.
 int build_batches(fdetd_plan_t P)
@@ -761,6 +889,7 @@ int build_batches(fdetd_plan_t P)
         b.ntiles = tiles;
         b.ntiles_ax = tiles_ax;
         if (!store_policy_applies(P, b)) b.nt_store = 0;
+        if (int rc = plan_fused(P, b, P->desc.data() + b.d0)) return rc;
         P->batches.push_back(b);
         t = u;
     }
@@ -1359,7 +1488,8 @@ int fdetd_plan(const fdetd_problem_desc *probs, int32_t n_probs, int32_t precisi
         const int per_stage = (b.nd < 0 && b.ntiles && b.ntiles_ax) ? 2 : 1;
         const int prepass = (flags & FDETD_PLAN_INCREMENT_FORM) ? 2 : 0;  // the two P passes
         const int staging = P->kind == FDETD_MAXWELL ? (fuse_wn(P, b, true) ? 1 : 2) : 0;  // J_rho, w_N
-        launches += (int64_t)(per_stage * b.N + staging + prepass) * (b.ntiles + b.ntiles_ax > 0);
+        const int stages = b.fused ? b.N / env_depth(b.nd) : b.N;
+        launches += (int64_t)(per_stage * stages + staging + prepass) * (b.ntiles + b.ntiles_ax > 0);
     }
     P->info.launches_per_step = launches;
     P->info.seg_rows = P->batches.empty() ? 0 : P->batches[0].seg;
@@ -1902,7 +2032,10 @@ int env_body(fdetd_plan_t P, void *vctx)
         for (size_t p = 0; p < P->probs.size(); ++p)
             chis[p] = (const char *)c.chi[p] + (size_t)(c.stride * s) * P->probs[p].cells * rb;
         for (size_t b = 0; b < P->batches.size() && !rc; ++b)
-            rc = enqueue_envelope_batch(P, P->batches[b], c.a, c.at, chis.data(), lane_stream(P, P->batches[b]));
+            rc = P->batches[b].fused ? enqueue_envelope_fused(P, P->batches[b], c.a, c.at, chis.data(), s, c.n_steps,
+                                                              lane_stream(P, P->batches[b]))
+                                     : enqueue_envelope_batch(P, P->batches[b], c.a, c.at, chis.data(),
+                                                              lane_stream(P, P->batches[b]));
     }
     const int rj = join_lanes(P);
     return rc ? rc : rj;
