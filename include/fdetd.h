@@ -127,7 +127,8 @@ typedef struct {
     double profiled_ms;          /* sum of their durations                                       */
     double profiled_bytes;       /* sum of their algorithmic HBM bytes                           */
     /* tiling of the first launch batch: rho rows per marching segment of the main launch and of the
-     * FP32C near-axis launch (0 without one), and the plan-time autotuning that picked them (0 ms: none) */
+     * FP32C near-axis launch (0 without one; small launches share a near-axis segment out over up to 4
+     * wavefronts), and the plan-time autotuning that picked them (0 ms: none) */
     int32_t seg_rows, seg_rows_axis;
     double autotune_ms;
     int32_t streams;  /* streams a step call runs on: 1, or up to 4 when the plan has several launch batches */

@@ -768,6 +768,25 @@ int axis_segment_rows()
     return kSegAxis;
 }
 
+// Wavefronts that share the rows of a near-axis segment.  A near-axis tile marches in FP64 arithmetic and is the
+// longest chain of a small launch, so there its rows are shared out; each wavefront fills a window of 2 N_D rows
+// of its own, which costs more than it gives once the chip is full.  By the cells of the plan, whose launches may
+// run side by side.  us per step with 1, 2, 4 wavefronts (Maxwell N = 6, envelope N = 4; order 16 | order 32):
+//   Maxwell   611 x 149, 1 mode   149 102  93 | 180 126 127        envelope  611 x 149       66 42 39 | 86 53 53
+//            1531 x 203, 1 mode   169 137 129 | 202 172 165                 1531 x 203       72 47 44 | 90 60 59
+//            2048 x 256, 1 mode   179 153 177 | 216 245 233                 3000 x 300       83 65 62 | 102 81 83
+//            1531 x 203, 2 modes  204 196 186 | 266 251 261                 2048 x 256, two  85 69 68 | 105 90 85
+//            3000 x 300, 1 mode   236 237 241 | 283 309 333                 3000 x 300, two 101 97 99 | 128 132 130
+// (order 8, whose band is one segment of 8 rows: alike).
+int axis_split(const fdetd_plan_t P)
+{
+    if (std::getenv("FDETD_SEG_AXIS")) return 1;
+    size_t cells = 0;
+    for (const Prob &q : P->probs) cells += q.cells;
+    const size_t small = P->kind == FDETD_MAXWELL ? (size_t)1 << 18 : (size_t)1 << 20;
+    return cells < small ? 4 : cells < 2 * small ? 2 : 1;
+}
+
 // FDETD_ENV_FUSE = 0 or 1 fixes whether envelope steps run in fused groups of stages; -1: unset.
 int forced_env_fuse()
 {
@@ -829,6 +848,7 @@ int build_batches(fdetd_plan_t P)
     // FDETD_PLAN_MIXED_WIDTHS: a batch holds problems of any stencil width (sorted by width inside it, so
     // that each XCD's contiguous tile range mostly runs one width's code); otherwise one width per batch
     const bool mixed = mixed_widths(P);
+    const int split = axis_split(P);
     std::stable_sort(order.begin(), order.end(), [&](int x, int y) {
         const auto &a = P->probs[x].d, &b = P->probs[y].d;
         if (!mixed && a.fd_order != b.fd_order) return a.fd_order < b.fd_order;
@@ -862,6 +882,10 @@ int build_batches(fdetd_plan_t P)
             const Prob &q = P->probs[order[v]];
             ProbDesc D;
             describe_problem(q.d, P->precision, seg, D);
+            if (D.ax_rows > 0) {
+                D.seg_ax = std::max(1, std::min(axis_segment_rows() / split, D.ax_rows));
+                D.nseg_ax = (D.ax_rows + D.seg_ax - 1) / D.seg_ax;
+            }
             D.tile_begin = tiles;
             D.tile_begin_ax = tiles_ax;
             D.tile_order = P->kind == FDETD_MAXWELL ? b.tile_order : 0;
@@ -1493,7 +1517,7 @@ int fdetd_plan(const fdetd_problem_desc *probs, int32_t n_probs, int32_t precisi
     }
     P->info.launches_per_step = launches;
     P->info.seg_rows = P->batches.empty() ? 0 : P->batches[0].seg;
-    P->info.seg_rows_axis = P->desc.empty() ? 0 : P->desc[0].seg_ax;
+    P->info.seg_rows_axis = P->desc.empty() ? 0 : std::min(axis_segment_rows(), P->desc[0].ax_rows);
     P->info.store_policy = P->batches.empty() ? 0 : P->batches[0].nt_store;
     P->info.tile_order = P->batches.empty() ? 0 : P->batches[0].tile_order;
     P->info.autotune_ms = tune_ms;
