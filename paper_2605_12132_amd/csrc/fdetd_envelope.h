@@ -26,14 +26,14 @@ constexpr size_t kEnvFuseCells = 1 << 20;  // in a launch; 2900 x 360, orders 2,
 constexpr int kEnvRows = 640;  // most rows of a march (output rows, and the rows before and behind them)
 constexpr int env_depth(int nd) { return nd == 1 ? 4 : 2; }
 constexpr int env_out_columns(int nd) { return kEnvWaves * 32 - 2 * (env_depth(nd) - 1) * nd; }
-struct EnvFuseArgs {
-    const ProbDesc *probs;
-    int nprob, ntiles;
+// Arguments of a group's launch: those of a stage (psi, aux, chi: the caller's planes) with role = ROLE_ENV_GROUP, by
+// which the stage launch hands them on, and
+constexpr int ROLE_ENV_GROUP = 3;
+struct EnvFuseArgs : BatchArgs {
     int seg;                       // rows per segment
     int sel_in, sel_psi, sel_out;  // vectors of the group: 0 the caller's planes, 1, 2 the plan's stage vectors
-    double coef[4];                // of the group's stages, in order
+    double coefs[4];               // of the group's stages, in order
     int begin[kMaxBatch];          // first tile of each problem
-    const void *a[kMaxBatch], *at[kMaxBatch], *chi[kMaxBatch];
 };
 hipError_t launch_envelope_fused(int nd, const EnvFuseArgs &a, hipStream_t s);
 

@@ -274,8 +274,8 @@ __device__ __forceinline__ void env_group(const EnvGroup &C, int o0, int k0, int
 // Vector `sel` of problem p: 0 the caller's planes, 1 and 2 the plan's two stage vectors.
 __device__ __forceinline__ void env_vector(const EnvFuseArgs &A, CDesc &D, int p, int sel, char *&a, char *&t)
 {
-    a = sel == 0 ? (char *)A.a[p] : (char *)D.buf[sel - 1];
-    t = sel == 0 ? (char *)A.at[p] : (char *)D.buf[sel - 1] + D.plane * sizeof(double2);
+    a = sel == 0 ? (char *)A.psi[p] : (char *)D.buf[sel - 1];
+    t = sel == 0 ? (char *)A.aux[p] : (char *)D.buf[sel - 1] + D.plane * sizeof(double2);
 }
 
 template <int ND, int S>
@@ -305,7 +305,7 @@ __global__ __launch_bounds__(kEnvWaves *WAVE) void k_envelope_group(EnvFuseArgs 
     C.pt = b;
     env_vector(A, D, p, A.sel_out, C.oa, C.ot);
     C.chi = (const char *)A.chi[p];
-    C.coef = A.coef;
+    C.coef = A.coefs;
     env_group<ND, S>(C, o0, k0, k1, lds);
 }
 

@@ -17,6 +17,7 @@
 //     as wave-uniform branches.
 // Tiles are numbered problem by problem and handed out so that each XCD (with its own L2) receives a
 // contiguous range of them: neighbouring tiles, whose halos overlap, share an L2.
+#include "fdetd_envelope.h"
 #include "fdetd_lanes.h"
 #include "fdetd_tiles.h"
 
@@ -1188,6 +1189,7 @@ hipError_t go_maxwell_any_v(const BatchArgs &a, hipStream_t s)
     template <>                                                                                      \
     hipError_t march_envelope_nd<N>(int prec, const BatchArgs &a, hipStream_t s)                     \
     {                                                                                                \
+        if (a.role == ROLE_ENV_GROUP) return launch_envelope_fused(N, static_cast<const EnvFuseArgs &>(a), s); \
         return prec == P64 ? go_envelope<double2, N>(a, s) : go_envelope<float2, N>(a, s);           \
     }                                                                                                \
     template <>                                                                                      \

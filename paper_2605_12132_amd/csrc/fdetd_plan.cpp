@@ -502,19 +502,14 @@ int enqueue_envelope_fused(fdetd_plan_t P, const Batch &b, void *const *a, void 
     const size_t eb = elem_bytes(P->precision);
     const int depth = env_depth(b.nd), groups = b.N / depth;
     EnvFuseArgs A{};
-    A.probs = P->ddesc + b.d0;
-    A.nprob = b.count;
+    const size_t cells = envelope_args(P, b, a, at, chi, A);
+    A.role = ROLE_ENV_GROUP;
     A.ntiles = b.fused;
     A.seg = b.fused_seg;
-    size_t cells = 0;
     for (int t = 0, begin = 0; t < b.count; ++t) {
         const fdetd_problem_desc &d = P->probs[b.members[t]].d;
         A.begin[t] = begin;
         begin += fused_tiles(d.nz, d.nr, A.seg, env_out_columns(b.nd));
-        A.a[t] = a[b.members[t]];
-        A.at[t] = at[b.members[t]];
-        A.chi[t] = chi[b.members[t]];
-        cells += P->probs[b.members[t]].cells;
     }
     const bool moved = step & 1;
     A.sel_psi = moved ? 2 : 0;
@@ -531,10 +526,10 @@ int enqueue_envelope_fused(fdetd_plan_t P, const Batch &b, void *const *a, void 
             break;
         }
         A.sel_out = (groups - 1 - g - tail) % 2 ? 1 : next;
-        for (int t = 0; t < depth; ++t) A.coef[t] = b.dt / (b.N - g * depth - t);
+        for (int t = 0; t < depth; ++t) A.coefs[t] = b.dt / (b.N - g * depth - t);
         // algorithmic bytes: vin (2c) + psi (2c; the same data in the first group) + chi + out (2c)
         if ((rc = profile_begin(P, ((g == 0 ? 4.0 : 6.0) + 0.5) * cells * eb))) return rc;
-        HIPCHK(P, launch_envelope_fused(b.nd, A, s));
+        HIPCHK(P, launch_envelope_march(P64, b.nd, A, s));
         if ((rc = profile_end(P))) return rc;
         A.sel_in = A.sel_out;
     }
