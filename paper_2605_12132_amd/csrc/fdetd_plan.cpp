@@ -1671,8 +1671,10 @@ int gather_impl(fdetd_plan_t plan, void *const *psi, const double *samples, int6
     G.dz = d0.dz;
     G.dr = d0.dr;
     // Destaggered components go to buf[0] (E_theta is read from psi); B_theta's z shift goes to buf[1] and
-    // its rho pass reads that, so it runs in the next launch, beside the independent passes of the next
-    // problem: np + 1 launches in all.
+    // its rho pass reads that, so it runs in the next launch.  A launch takes the independent passes of as many
+    // problems as its pass list and its two coefficient sets hold (the modes of a grid mostly have one stencil:
+    // all of them), beside the rho passes of the launch before: each launch fills and drains the chip once
+    // (4096 x 512, three modes, order 16, 10^6 samples: four launches of 16 us, now two of 27).
     DestaggerArgs X;
     std::memset(&X, 0, sizeof X);
     X.nz = d0.nz;
@@ -1692,30 +1694,40 @@ int gather_impl(fdetd_plan_t plan, void *const *psi, const double *samples, int6
         pS = (m % 2 == 0) ? 1 : -1;
         pA = (std::abs(m - 1) % 2 == 0) ? 1 : -1;
     };
-    for (int p = 0; p <= np; ++p) {
+    int p = 0;
+    for (std::vector<int> before, now; p < np || !before.empty(); before.swap(now)) {
         X.npass = 0;
+        int sets = 0;
+        auto set_of = [&](const Prob &q) {  // -1: both sets hold other widths
+            for (int set = 0; set < sets; ++set)
+                if (X.nd[set] == q.nd) return set;
+            if (sets == 2) return -1;
+            coeffs(sets, q);
+            return sets++;
+        };
         auto add = [&](const void *src, void *dst, int rho, int parity, int extrapolate, int grow_r, int set) {
             X.pass[X.npass++] = DestaggerPass{src, dst, rho, parity, extrapolate, 0, grow_r, set};
         };
-        if (p > 0) {  // B_theta's rho pass of the previous problem
-            const Prob &q = plan->probs[p - 1];
-            int pS, pA;
+        int pS, pA;
+        for (int b : before) {  // B_theta's rho passes of the launch before
+            const Prob &q = plan->probs[b];
             parities(q.d.m, pS, pA);
-            coeffs(1, q);
-            add(plane(q, q.buf[1], 0), plane(q, q.buf[0], BTH), 1, pA, q.d.m == 1, 0, 1);
+            add(plane(q, q.buf[1], 0), plane(q, q.buf[0], BTH), 1, pA, q.d.m == 1, 0, set_of(q));
         }
-        if (p < np) {
+        now.clear();
+        for (; p < np && X.npass + 5 <= kMaxDestaggerPass; ++p) {
             const Prob &q = plan->probs[p];
-            int pS, pA;
+            const int set = set_of(q);
+            if (set < 0) break;
             parities(q.d.m, pS, pA);
-            coeffs(0, q);
-            add(plane(q, psi[p], ER), plane(q, q.buf[0], ER), 1, pA, q.d.m == 1, 0, 0);
-            add(plane(q, psi[p], EZ), plane(q, q.buf[0], EZ), 0, 1, 0, 0, 0);
-            add(plane(q, psi[p], BR), plane(q, q.buf[0], BR), 0, 1, 0, 0, 0);
-            add(plane(q, psi[p], BTH), plane(q, q.buf[1], 0), 0, 1, 0, q.nd, 0);  // read at +-nd rows next
-            add(plane(q, psi[p], BZ), plane(q, q.buf[0], BZ), 1, pS, q.d.m == 0, 0, 0);
+            add(plane(q, psi[p], ER), plane(q, q.buf[0], ER), 1, pA, q.d.m == 1, 0, set);
+            add(plane(q, psi[p], EZ), plane(q, q.buf[0], EZ), 0, 1, 0, 0, set);
+            add(plane(q, psi[p], BR), plane(q, q.buf[0], BR), 0, 1, 0, 0, set);
+            add(plane(q, psi[p], BTH), plane(q, q.buf[1], 0), 0, 1, 0, q.nd, set);  // read at +-nd rows next
+            add(plane(q, psi[p], BZ), plane(q, q.buf[0], BZ), 1, pS, q.d.m == 0, 0, set);
             G.m[p] = q.d.m;
             for (int c = 0; c < 6; ++c) G.plane[p][c] = c == ETH ? plane(q, psi[p], ETH) : plane(q, q.buf[0], c);
+            now.push_back(p);
         }
         HIPCHK(plan, launch_destagger(prec, X, plan->stream));
     }
