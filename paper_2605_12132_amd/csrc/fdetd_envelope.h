@@ -22,7 +22,7 @@ constexpr int kEnvWaves = 4;
 constexpr int kEnvBlocks = 512;           // blocks that run at a time: two per CU
 constexpr int kEnvFuseND = 4;
 constexpr size_t kEnvFuseCells = 1 << 20;  // in a launch; 2900 x 360, orders 2, 4, 6, 8: 72, 75, 77, 79 us per 4
-                                           // stages one by one, 41, 57, 60, 71 fused; 2048 x 256, order 8: 49, 53
+                                           // stages one by one, 40, 55, 60, 70 fused; 2048 x 256, order 8: 49, 53
 constexpr int kEnvRows = 640;  // most rows of a march (output rows, and the rows before and behind them)
 constexpr int env_depth(int nd) { return nd == 1 ? 4 : 2; }
 constexpr int env_out_columns(int nd) { return kEnvWaves * 32 - 2 * (env_depth(nd) - 1) * nd; }

@@ -13,11 +13,12 @@
 // N_D = 1: one).  Columns beside the grid and rows beyond it are read at the nearest cell of the grid and replaced
 // by zeros.
 //
-// What bounds it (order 8, FP64, 4096 x 512, a step of 4 stages: 137 us stage by stage, 115 us fused; 6000 x 700,
-// whose planes leave the caches: 355 and 231 us; order 2: 346 and 138 us): no longer the bytes (3.2 TB/s) but
-// issue, at half of the vector rate with two wavefronts per SIMD, and the rows and columns formed twice (a fifth
-// at this size).  Two blocks of four wavefronts per CU are as fast as one of eight (867 and 877 us per 8 steps)
-// and faster than three (910: shorter segments) or one of twelve (934); one barrier per row 867, per two rows 836.
+// What bounds it (order 8, 4096 x 512, a step of 4 stages: 137 us stage by stage, 109 us fused; 6000 x 700, whose
+// planes leave the caches: 355 and 217 us; order 2: 345 and 134 us): no longer the bytes (249 MB per group past
+// the L2, 4.5 TB/s) but issue, with two wavefronts per SIMD and the vector unit busy 42 % of the time, and the rows
+// and columns formed twice (a fifth at this size).  Two blocks of four wavefronts per CU are as fast as one of eight
+// (867 and 877 us per 8 steps) and faster than three (910: shorter segments) or one of twelve (934); one barrier per
+// row 867, per two rows 836.
 #include "fdetd_envelope.h"
 #include "fdetd_lanes.h"
 
