@@ -21,8 +21,14 @@ namespace fdetd {
 constexpr int kEnvWaves = 4;
 constexpr int kEnvBlocks = 512;           // blocks that run at a time: two per CU
 constexpr int kEnvFuseND = 4;
-constexpr size_t kEnvFuseCells = 1 << 20;  // in a launch; 2900 x 360, orders 2, 4, 6, 8: 72, 75, 77, 79 us per 4
-                                           // stages one by one, 40, 55, 60, 70 fused; 2048 x 256, order 8: 49, 53
+// Fewest cells of a launch.  us per step of 4 stages one by one | fused, in calls of 1 and of 2 steps:
+//                  order 2         order 4         order 6         order 8
+//   1400 x 180   30 | 35 27      32 | 32 32      32 | 37 38      34 | 38 41
+//   2048 x 256   44 | 44 29      45 | 43 41      46 | 45 43      48 | 50 52
+//   2400 x 300   56 | 49 34      58 | 50 42      59 | 55 49      60 | 57 54
+//   2900 x 360   72 | 61 40      75 | 66 55      77 | 69 60      79 | 76 70
+// (the waves of a small launch wait for the longest march, whatever it saves)
+constexpr size_t env_fuse_cells(int nd) { return nd <= 3 ? 1 << 19 : 700000; }
 constexpr int kEnvRows = 640;  // most rows of a march (output rows, and the rows before and behind them)
 constexpr int env_depth(int nd) { return nd == 1 ? 4 : 2; }
 constexpr int env_out_columns(int nd) { return kEnvWaves * 32 - 2 * (env_depth(nd) - 1) * nd; }

@@ -798,7 +798,7 @@ int plan_fused(fdetd_plan_t P, Batch &b, const ProbDesc *D)
     size_t cells = 0;
     for (int t = 0; t < b.count; ++t) cells += D[t].plane;
     const int force = forced_env_fuse();
-    if (force == 0 || (force < 0 && cells < kEnvFuseCells)) return FDETD_OK;
+    if (force == 0 || (force < 0 && cells < env_fuse_cells(b.nd))) return FDETD_OK;
     // rows per segment: a block marches them and the rows before its first one, kEnvBlocks at a time
     const int lag = (env_depth(b.nd) - 1) * b.nd, oc = env_out_columns(b.nd);
     double least = 1e300;
