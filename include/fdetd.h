@@ -279,7 +279,7 @@ FDETD_API int fdetd_deposit_jz(fdetd_plan_t plan, const double *samples, int64_t
  *   j_half   n_probs device pointers to current blocks as for fdetd_step (3 planes, 4 with
  *            FDETD_PLAN_CURRENT_CORRECTION), the plan's precision.
  * Enqueue only; atomic adds.  Blocks of up to 1024 consecutive samples order their samples by cell, sum those of
- * one cell first and add the sums in an FP64 LDS tile where their shapes touch at most 1232 cells of a grid (668
+ * one cell first and add the sums in an FP64 LDS tile where their shapes touch at most 1232 cells of a grid (1124
  * with rho_xy): position-ordered samples are much faster. */
 FDETD_API int fdetd_deposit_current(fdetd_plan_t plan, const double *samples, int64_t n, double eps,
                                     void *const *j_half);

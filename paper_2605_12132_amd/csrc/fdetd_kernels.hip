@@ -830,15 +830,18 @@ __device__ __noinline__ void deposit_sample_wide(double eps, bool rho_xy, const 
 //      of a shape against up to 12 columns), and adds the sums of a finished run to the block's LDS tile;
 //   4. adds the tile to the planes, one global atomic per touched value.
 // A block whose samples touch more cells than the tile holds adds the sums of its runs to the planes.  Where runs
-// are short (more than DEPC_RUNS among 64 samples: the ends of a bunch, or samples in no order) each lane adds its
-// own sample instead: a run costs about as much as 64 lanes' samples together, and the sparse end blocks set the
-// kernel's time (without this path 1150 us; DEPC_RUNS 4 / 8 / 12 / 20: 522 / 426 / 408 / 449 us; blocks of 512
-// and 256 samples 510 and 614 us).  10^6 samples of a bunch, three modes of an 8192 x 1024 grid, FP64: 945 -> 408 us.
+// are short (the ends of a bunch, or samples in no order) each lane adds its own sample instead.  A lane's adds grow
+// with the modes and those of a run, which holds them all in its columns, do not: the limit is DEPC_RUNS runs per
+// mode among the CH samples a wavefront takes at a time (10^6 samples of a bunch 25 rows wide, with 3 / 4 / 6 runs
+// per mode: one mode 329 / 309 / 321 us, three 846 / 770 / 729 us; with rho_xy one mode 465 / 469 / 513 us, three
+// 1371 / 1295 / 1337 us; 12 whatever the modes: 379, 783, 617, 1880 us).  10^6 samples of a bunch, three modes of an
+// 8192 x 1024 grid, FP64: 945 -> 395 us (without lanes of their own 1150 us; blocks of 512 and 256 samples 510 and
+// 614 us).
 constexpr int DEPC_THREADS = 256, DEPC_WAVES = DEPC_THREADS / 64, DEPC_MAX = 1024;  // most samples per block
 constexpr int DEPC_MODES = 3;       // modes per pass: two components of each in 16 columns
 constexpr int DEPC_ROWS = 128;      // rows of the table of radial factors
 constexpr int DEPC_BINS = 8192;     // most bins of the sort
-constexpr int DEPC_RUNS = 12;       // more runs among 64 samples: a lane per sample (short runs do not repay step 3)
+constexpr int DEPC_RUNS = 4;        // more runs per mode in a chunk: a lane per sample (short runs do not repay step 3)
 constexpr int DEPC_LDS = 163840 - 2048 - DEPC_ROWS * 16 - 256;  // what records and tile share (160 KiB per CU)
 // record: radial weights at the sample, at +, at - (4 each), z weights (4), integrated z weights (8), then the
 // columns of the products: the angular factors times v_rho, times v_theta (6 each), those at + and at - (6 each);
@@ -848,10 +851,12 @@ typedef double v4d __attribute__((ext_vector_type(4)));
 template <typename R, bool RXY>
 __global__ __launch_bounds__(DEPC_THREADS) void k_deposit_current(DepositArgs A)
 {
-    constexpr int NPL = RXY ? 4 : 3, NG = DEPC_MODES, REC = RXY ? 57 : 49;
-    constexpr int TILE = (DEPC_LDS - DEPC_WAVES * 64 * REC * 8) / 8 & ~1, MAX_CELLS = TILE / (2 * NPL);
+    // (records of CH samples per wavefront at a time: with rho_xy 64 would leave the tile 668 cells)
+    constexpr int NPL = RXY ? 4 : 3, NG = DEPC_MODES, REC = RXY ? 57 : 49, CH = RXY ? 48 : 64;
+    constexpr int TILE = (DEPC_LDS - DEPC_WAVES * CH * REC * 8) / 8 & ~1, MAX_CELLS = TILE / (2 * NPL);
+    static_assert(MAX_CELLS >= 1024, "a tile holds the footprint of a block of samples in position order");
     __shared__ double tile[TILE];
-    __shared__ double rec[DEPC_WAVES][64][REC];
+    __shared__ double rec[DEPC_WAVES][CH][REC];
     __shared__ double2 rtab[DEPC_ROWS];  // rho_k^(eps-1), and the row's weight in the normalisation
     __shared__ unsigned short order[DEPC_MAX];
     __shared__ int red[4 * DEPC_WAVES + 1];
@@ -983,14 +988,18 @@ __global__ __launch_bounds__(DEPC_THREADS) void k_deposit_current(DepositArgs A)
             const int m_a = A.probs[p0 + g0 + min(g_a, ng - 1)].m, m_j = A.probs[p0 + g0 + min(g_j, ng - 1)].m;
             R *const j_a = (R *)A.j[p0 + g0 + min(g_a, ng - 1)], *const j_j = (R *)A.j[p0 + g0 + min(g_j, ng - 1)];
             const bool on_a = col < 12 && g_a < ng && (m_a != 0 || part == 0), on_j = col < 6 && g_j < ng && (m_j != 0 || part == 0);
-            // adds the sums d[r] of rows b + r at node i; the rows below the axis are first folded onto rows -1 - q
-            // (opposite parts of a sample on the axis then cancel exactly)
-            auto add = [&](bool on, int pl, int g, R *jp, double fold, int b, int i, v4d d) {
+            // sums d[r] of rows b + r with the rows below the axis folded onto rows -1 - q (opposite parts of a
+            // sample on the axis then cancel exactly)
+            auto folded = [](v4d d, double fold, int b) {
                 if (b == -1) d[1] += fold * d[0];
                 if (b == -2) {
                     d[3] += fold * d[0];
                     d[2] += fold * d[1];
                 }
+                return d;
+            };
+            // adds the sums d[r] of rows b + r at node i
+            auto add = [&](bool on, int pl, int g, R *jp, int b, int i, v4d d) {
                 if (!on || i < 0 || i >= nz) return;
                 const bool in_z = cells > 0 && i >= fp[0] && i <= fp[1];
 #pragma unroll
@@ -1008,26 +1017,38 @@ __global__ __launch_bounds__(DEPC_THREADS) void k_deposit_current(DepositArgs A)
             auto flush = [&]() {
                 if (cur.x == INT_MIN) return;
                 const int bp = cur.y + (cur.z >> 16), bm = bp + (int)(short)(cur.z & 0xffff);
-                add(on_a, comp, g_a, j_a, fold_mA(m_a), cur.y, cur.x + node, dA);
+                add(on_a, comp, g_a, j_a, cur.y, cur.x + node, folded(dA, fold_mA(m_a), cur.y));
                 const double fs = fold_mS(m_j);
-                if (bp == bm) {  // both positions in the same rows
-                    add(on_j, 2, g_j, j_j, fs, bp, cur.w + node, dP0 + dM0);
-                    add(on_j, 2, g_j, j_j, fs, bp, cur.w + 4 + node, dP1 + dM1);
-                } else {
-                    add(on_j, 2, g_j, j_j, fs, bp, cur.w + node, dP0);
-                    add(on_j, 2, g_j, j_j, fs, bp, cur.w + 4 + node, dP1);
-                    add(on_j, 2, g_j, j_j, fs, bm, cur.w + node, dM0);
-                    add(on_j, 2, g_j, j_j, fs, bm, cur.w + 4 + node, dM1);
-                }
+                // Sums p of rows bp + r and m of rows bm + r: on a row that both positions touch they are joined in
+                // FP64.  In rho_xy, their difference, all but a part in v dt / drho of them cancels there: added
+                // one by one into a float plane (no tile) they left 3e-5 of it instead of 3e-8 (v = 0.01).
+                auto add_both = [&](int pl, int i, v4d p, v4d m) {
+                    if (bp == bm) {
+                        add(on_j, pl, g_j, j_j, bp, i, folded(p + m, fs, bp));
+                        return;
+                    }
+                    p = folded(p, fs, bp);
+                    m = folded(m, fs, bm);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q)
+                            if (bp + r == bm + q) {
+                                p[r] += m[q];
+                                m[q] = 0.0;
+                            }
+                    add(on_j, pl, g_j, j_j, bp, i, p);
+                    add(on_j, pl, g_j, j_j, bm, i, m);
+                };
+                add_both(2, cur.w + node, dP0, dM0);
+                add_both(2, cur.w + 4 + node, dP1, dM1);
                 if constexpr (RXY) {
-                    add(on_j, 3, g_j, j_j, fs, bp, cur.w + node, dX0);
-                    add(on_j, 3, g_j, j_j, fs, bp, cur.w + 4 + node, dX1);
-                    add(on_j, 3, g_j, j_j, fs, bm, cur.w + node, -dY0);
-                    add(on_j, 3, g_j, j_j, fs, bm, cur.w + 4 + node, -dY1);
+                    add_both(3, cur.w + node, dX0, -dY0);
+                    add_both(3, cur.w + 4 + node, dX1, -dY1);
                 }
             };
-            for (int c0 = w0; c0 < w1; c0 += 64) {
-                const int nc = min(64, w1 - c0);
+            for (int c0 = w0; c0 < w1; c0 += CH) {
+                const int nc = min(CH, w1 - c0);
                 int4 key{INT_MIN, 0, 0, 0};
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
                 if (lane < nc) {
@@ -1118,8 +1139,9 @@ __global__ __launch_bounds__(DEPC_THREADS) void k_deposit_current(DepositArgs A)
                 // runs of equal cells among the chunk's samples
                 const int px = __shfl_up(key.x, 1), py = __shfl_up(key.y, 1), pz = __shfl_up(key.z, 1), pw = __shfl_up(key.w, 1);
                 unsigned long long starts = __ballot(lane < nc && (lane == 0 || key.x != px || key.y != py || key.z != pz || key.w != pw));
-                if (__popcll(starts) > DEPC_RUNS) {
+                if (__popcll(starts) > DEPC_RUNS * ng) {
                     // many short runs: every lane adds its own sample, node by node
+                    const int slots = __ballot(key.x != INT_MIN && (key.z & 0xffff)) ? 8 : 4;  // bm != bp somewhere
                     if (lane < nc && key.x != INT_MIN) {
                         const double *r = rec[wv][lane];
                         const int bp = key.y + (key.z >> 16), bm = bp + (int)(short)(key.z & 0xffff);
@@ -1139,37 +1161,41 @@ __global__ __launch_bounds__(DEPC_THREADS) void k_deposit_current(DepositArgs A)
                                     if (m) atomicAdd(o + 1, (R)im);
                                 }
                             };
-                            // weight of row b + rr with the row below the axis that folds onto it
-                            auto weight = [&](int base, int b, int rr, double fold) {
-                                const int mirror = -1 - 2 * b - rr;
-                                const double w = r[base + rr];
-                                return mirror >= 0 && mirror < 4 && b + mirror < 0 ? w + fold * r[base + mirror] : w;
+                            // weight of row k among rows b .. b + 3, with the row below the axis that folds onto it
+                            auto weight = [&](int base, int b, int k, double fold) {
+                                const int mirror = -1 - k - b;
+                                double w = (unsigned)(k - b) < 4u ? r[base + k - b] : 0.0;
+                                if ((unsigned)mirror < 4u) w += fold * r[base + mirror];
+                                return w;
                             };
                             const double fa = fold_mA(m), fs = fold_mS(m);
                             const double *c = r + RC_CA + 2 * g;
 #pragma unroll 1
                             for (int rr = 0; rr < 4; ++rr) {
-                                const double w = weight(RC_R0, key.y, rr, fa);
-                                const double wp = weight(RC_RP, bp, rr, fs), wm = weight(RC_RM, bm, rr, fs);
+                                const double w = weight(RC_R0, key.y, key.y + rr, fa);
                                 for (int v = 0; v < 4; ++v) {
                                     const double t = w * r[RC_WZ + v];
                                     put(0, key.y + rr, key.x + v, t * c[0], t * c[1]);
                                     put(1, key.y + rr, key.x + v, t * c[6], t * c[7]);
                                 }
+                            }
+                            // rows of the + position, then those of the - position beside them; both positions'
+                            // parts of a row are joined before they are added, each product rounded as in the
+                            // other so that equal ones cancel
+#pragma unroll 1
+                            for (int rr = 0; rr < slots; ++rr) {
+#pragma clang fp contract(off)
+                                const int k = rr < 4 ? bp + rr : bm + rr - 4;
+                                if (rr >= 4 && (unsigned)(k - bp) < 4u) continue;
+                                const double wp = weight(RC_RP, bp, k, fs), wm = weight(RC_RM, bm, k, fs);
                                 const double pr = wp * r[RC_AP + 2 * g], pi = wp * r[RC_AP + 2 * g + 1];
                                 const double mr = wm * r[RC_AM + 2 * g], mi = wm * r[RC_AM + 2 * g + 1];
                                 for (int v = 0; v < 8; ++v) {
                                     const double f = r[RC_DF + v];
-                                    if (bp == bm) {
-                                        put(2, bp + rr, key.w + v, f * (pr + mr), f * (pi + mi));
-                                    } else {
-                                        put(2, bp + rr, key.w + v, f * pr, f * pi);
-                                        put(2, bm + rr, key.w + v, f * mr, f * mi);
-                                    }
+                                    put(2, k, key.w + v, f * (pr + mr), f * (pi + mi));
                                     if constexpr (RXY) {
                                         const double sz = r[RC_SZ + v];
-                                        put(3, bp + rr, key.w + v, sz * pr, sz * pi);
-                                        put(3, bm + rr, key.w + v, -sz * mr, -sz * mi);
+                                        put(3, k, key.w + v, sz * (pr - mr), sz * (pi - mi));
                                     }
                                 }
                             }
@@ -1181,7 +1207,8 @@ __global__ __launch_bounds__(DEPC_THREADS) void k_deposit_current(DepositArgs A)
                     const int i0 = __ffsll((long long)starts) - 1;
                     starts &= starts - 1;
                     const int i1 = starts ? __ffsll((long long)starts) - 1 : nc;
-                    const int4 k{__shfl(key.x, i0), __shfl(key.y, i0), __shfl(key.z, i0), __shfl(key.w, i0)};
+                    const int4 k{__builtin_amdgcn_readlane(key.x, i0), __builtin_amdgcn_readlane(key.y, i0),
+                                 __builtin_amdgcn_readlane(key.z, i0), __builtin_amdgcn_readlane(key.w, i0)};
                     if (k.x != cur.x || k.y != cur.y || k.z != cur.z || k.w != cur.w) {
                         flush();
                         cur = k;
