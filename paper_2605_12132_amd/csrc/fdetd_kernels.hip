@@ -550,6 +550,13 @@ __device__ __forceinline__ double rk_pow(double rk, double e)
 __device__ __forceinline__ double fold_mS(int m) { return m > 1 ? -1.0 : (m % 2 == 0 ? 1.0 : -1.0); }
 __device__ __forceinline__ double fold_mA(int m) { return m > 1 ? -1.0 : (m == 1 ? 1.0 : -1.0); }
 
+// Row that rho lies in: at most 8 rows beyond the grid, where a shape touches none of its rows (the row of a rho
+// beyond the range of int would wrap round), and 0 for a rho that is not a number.
+__device__ __forceinline__ int shape_row(const ProbDesc &D, double rho)
+{
+    return rho >= 0.0 ? (int)fmin(rho / D.dr, D.nr + 8.0) : 0;
+}
+
 // Radial shape of a sample at rho on the primary rows k = kc - 3 + j, j = 0..6 (folded with parity par,
 // normalised by N; w[j] = 0 off [k0, k1]) and the angular shape of mode m at the sample's angle theta,
 // given by (x, y): e^(-i m theta) as the m-th power of (x - i y) / rho (theta = 0 on the axis).  Each
@@ -564,7 +571,7 @@ __device__ __forceinline__ SampleShape sample_shape(const ProbDesc &D, double rh
 {
     SampleShape S;
     const double dr = D.dr;
-    S.kc = (int)floor(rho / dr);
+    S.kc = shape_row(D, rho);
     S.k0 = S.kc - 3 > 0 ? S.kc - 3 : 0;
     S.k1 = S.kc + 3 < D.nr - 1 ? S.kc + 3 : D.nr - 1;
     double N = 0.0;
@@ -581,7 +588,10 @@ __device__ __forceinline__ SampleShape sample_shape(const ProbDesc &D, double rh
     }
     const double inv = 1.0 / N;
 #pragma unroll
-    for (int j = 0; j < 7; ++j) S.w[j] *= inv;
+    for (int j = 0; j < 7; ++j) {  // (N = 0 far beyond the grid, NaN for a NaN: still nothing off [k0, k1])
+        const int k = S.kc - 3 + j;
+        S.w[j] = k >= S.k0 && k <= S.k1 ? S.w[j] * inv : 0.0;
+    }
     if (D.m == 0) {
         S.ar = 0.5 / M_PI;
         S.ai = 0.0;
@@ -598,11 +608,9 @@ __device__ __forceinline__ SampleShape sample_shape(const ProbDesc &D, double rh
     }
     return S;
 }
-// The z shape of a position x (in cells) spans nodes floor(x) - 1 .. floor(x) + 2, which must lie on the grid.
-__device__ __forceinline__ bool z_on_grid(const ProbDesc &D, double x)
-{
-    return (int)floor(x) - 1 >= 0 && (int)floor(x) + 2 <= D.nz - 1;
-}
+// The z shape of a position x (in cells) spans nodes floor(x) - 1 .. floor(x) + 2, which must lie on the grid
+// (compared as reals: the node of a position beyond the range of int would wrap round).
+__device__ __forceinline__ bool z_on_grid(const ProbDesc &D, double x) { return x >= 1.0 && x < D.nz - 2.0; }
 
 // Block-wide min and max of four ints (NW wave64 wavefronts), through LDS (red holds 4 NW ints).
 template <int NW = 4>
@@ -708,7 +716,7 @@ __global__ __launch_bounds__(256) void k_deposit_jz(DepositArgs A)
             // more than 8 nodes: deposited by deposit_z_wide, outside the block's tile
             wide[u] = hi[u] - lo[u] + 1 > 8;
             if (wide[u]) continue;
-            const int kc = (int)floor(sm[u].rho / D.dr);
+            const int kc = shape_row(D, sm[u].rho);
             fp[0] = min(fp[0], lo[u]);
             fp[1] = max(fp[1], hi[u]);
             fp[2] = min(fp[2], max(kc - 3, 0));
@@ -1275,7 +1283,7 @@ __global__ __launch_bounds__(256) void k_deposit_rho(DepositArgs A)
             const double zc = (A.samples[4 * s] + A.shift) / D.dz;
             if (!z_on_grid(D, zc)) continue;
             const double x = A.samples[4 * s + 1], y = A.samples[4 * s + 2];
-            const int kc = (int)floor(sqrt(x * x + y * y) / D.dr);
+            const int kc = shape_row(D, sqrt(x * x + y * y));
             fp[0] = min(fp[0], (int)floor(zc) - 1);
             fp[1] = max(fp[1], (int)floor(zc) + 2);
             fp[2] = min(fp[2], max(kc - 3, 0));

@@ -1,0 +1,71 @@
+"""Samples that a program has lost -- infinite, beyond the range of int in cells, not a number -- deposit inside the
+planes only: off the grid they add nothing, and a NaN transverse position puts NaN into rows 0 .. 3 of its own z nodes
+and nowhere else.  The ordinary samples beside them deposit what they do alone (FP64 atomics in another order: 1e-12)."""
+import numpy as np
+import pytest
+
+from helpers import dev, log, rel_l2
+
+import paper_2605_12132_amd as F
+import paper_2605_12132_amd.inputs as I
+
+pytestmark = pytest.mark.gpu
+DZ = I.LAMBDA0 / 20
+NZ, NR, DT = 120, 40, 0.5 * DZ
+FAR = [1e10, 1e300, np.inf]  # rho or z; 1e10 DZ: more than 2^31 cells
+
+
+def ordinary(n, rng, velocity):
+    z, r, th = rng.uniform(60, 110, n) * DZ, rng.uniform(0, 30, n) * 2 * DZ, rng.uniform(-np.pi, np.pi, n)
+    cols = [z, r * np.cos(th), r * np.sin(th), rng.uniform(0.5, 1, n)]
+    return np.column_stack(cols + [rng.uniform(-0.5, 0.5, (n, 3)), np.zeros(n)] if velocity else cols)
+
+
+def deposit(kind, s, precision):
+    import torch
+    cd = torch.complex128 if precision == F.FP64 else torch.complex64
+    flags = F.PLAN_SKIP_STABILITY | (F.PLAN_CURRENT_CORRECTION if kind == "current" else 0)
+    plan = F.Plan([F.Problem(NZ, NR, m, 8, 8, DZ, 2 * DZ, DT) for m in (0, 1)], precision=precision, flags=flags)
+    J = [torch.zeros(({"rho": 1, "jz": 3, "current": 4}[kind], NR, NZ), dtype=cd, device="cuda") for _ in range(2)]
+    d = dev(s, torch.float64)
+    if kind == "jz":
+        plan.deposit_jz(d, J, vz=0.9)
+    elif kind == "rho":
+        plan.deposit_rho(d, [j[0] for j in J])
+    else:
+        plan.deposit_current(d, J)
+    torch.cuda.synchronize()
+    plan.close()
+    return np.stack([j.cpu().numpy().astype(np.complex128) for j in J])
+
+
+def lost(kind, value):
+    """Samples lost in z, then in rho (at z node 20)."""
+    rows = [[v, 2 * DZ, 0.0, 1.0] for v in (value, -value)]
+    rows += [[20.5 * DZ, a, b, 1.0] for a, b in ((value, 0.0), (0.0, -value), (value, value))]
+    return np.array([r + [0.2, 0.1, 0.5, 0.0] for r in rows] if kind == "current" else rows)
+
+
+@pytest.mark.parametrize("precision", [F.FP64, F.FP32C])
+@pytest.mark.parametrize("kind", ["jz", "rho", "current"])
+@pytest.mark.parametrize("value", FAR)
+def test_far_samples_add_nothing(kind, value, precision):
+    print(f"far samples {kind} {value}", flush=True)
+    rng = np.random.default_rng(3)
+    s, far = ordinary(300, rng, kind == "current"), lost(kind, value)
+    assert not np.any(deposit(kind, far, precision))
+    got, want = deposit(kind, np.concatenate([s[:100], far, s[100:]]), precision), deposit(kind, s, precision)
+    assert rel_l2(got, want) < (1e-12 if precision == F.FP64 else 1e-5)
+
+
+@pytest.mark.parametrize("precision", [F.FP64, F.FP32C])
+@pytest.mark.parametrize("kind", ["jz", "rho"])
+def test_nan_position(kind, precision):
+    print(f"NaN samples {kind}", flush=True)
+    s = ordinary(300, np.random.default_rng(4), False)
+    bad = np.array([[20.5 * DZ, np.nan, DZ, 1.0], [np.nan, DZ, DZ, 1.0]])
+    got, want = deposit(kind, np.concatenate([s, bad]), precision), deposit(kind, s, precision)
+    nan = np.isnan(got)
+    log(f"  NaN in rows {np.unique(np.nonzero(nan)[2])}, columns {np.unique(np.nonzero(nan)[3])}")
+    assert nan.any() and not nan[:, :, 4:].any() and not nan[..., :18].any() and not nan[..., 25:].any()
+    assert rel_l2(np.where(nan, 0, got), np.where(nan, 0, want)) < (1e-12 if precision == F.FP64 else 1e-5)
