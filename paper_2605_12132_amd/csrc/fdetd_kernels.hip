@@ -801,6 +801,7 @@ __device__ __noinline__ void deposit_sample_wide(double eps, bool rho_xy, const 
         const int lo = (int)floor(zc) - 1;
         for (int jr = 0; jr < 7; ++jr) {
             const int k = S0.kc - 3 + jr;
+            if (S0.w[jr] == 0.0) continue;  // a row off the grid, whatever the weight
             for (int u = 0; u < 4; ++u) {
                 const double w = qw * bspline3(lo + u - zc) * inv_dz * S0.w[jr];
                 if (w == 0.0) continue;

@@ -69,3 +69,14 @@ def test_nan_position(kind, precision):
     log(f"  NaN in rows {np.unique(np.nonzero(nan)[2])}, columns {np.unique(np.nonzero(nan)[3])}")
     assert nan.any() and not nan[:, :, 4:].any() and not nan[..., :18].any() and not nan[..., 25:].any()
     assert rel_l2(np.where(nan, 0, got), np.where(nan, 0, want)) < (1e-12 if precision == F.FP64 else 1e-5)
+
+
+@pytest.mark.parametrize("precision", [F.FP64, F.FP32C])
+def test_nan_weight_of_a_fast_sample_stays_on_the_grid(precision):
+    """More than 3 cells in a step, next to the axis: no row below the grid is added to."""
+    s = ordinary(300, np.random.default_rng(7), True)
+    bad = np.array([[20.5 * DZ, 0.7 * DZ, DZ, np.nan, 0.2, 0.1, 10.0, 0.0]])
+    got, want = deposit("current", np.concatenate([s[:7], bad, s[7:]]), precision), deposit("current", s, precision)
+    nan = np.isnan(got)
+    assert nan[:, 0].any() and not nan[:, :, 5:].any() and not nan[..., :16].any() and not nan[..., 27:].any()
+    assert rel_l2(np.where(nan, 0, got), np.where(nan, 0, want)) < (1e-12 if precision == F.FP64 else 1e-5)
