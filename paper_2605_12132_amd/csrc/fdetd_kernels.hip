@@ -784,7 +784,7 @@ __global__ __launch_bounds__(256) void k_deposit_jz(DepositArgs A)
 }
 
 // All currents of one sample, added node by node with global atomics: samples that move more than 3 cells in a
-// step, whose shapes do not fit the block's tile.
+// step, whose shapes do not fit the block's tile, and samples with a value that is not a number or not finite.
 template <typename R>
 __device__ __noinline__ void deposit_sample_wide(double eps, bool rho_xy, const ProbDesc *Dp, R *j, const double *q)
 {
@@ -887,6 +887,12 @@ __global__ __launch_bounds__(DEPC_THREADS) void k_deposit_current(DepositArgs A)
         const double h = 0.5 * D.dt, dz = D.dz, dr = D.dr;
         const int nz = D.nz, nr = D.nr;
         const size_t plane = D.plane;
+        // Numbers that no product of a sample's factors can overflow.  A sample with others is added by itself: a NaN
+        // position has no cell to be sorted by, and in a product of factors an infinite weight would meet the zeros
+        // of components that the sample does not have (J_rho of a sample at rest).
+        auto plain = [](const double *q) {
+            return fabs(q[1]) + fabs(q[2]) + fabs(q[3]) + fabs(q[4]) + fabs(q[5]) < 1e100;
+        };
         auto base_row = [&](double rc) { return (int)floor(rc - 0.5) - 1; };  // rows b .. b + 3, rc = rho / dr
         // footprint of the block's samples
         int fp[4] = {INT_MAX, INT_MIN, INT_MAX, INT_MIN};  // zmin, zmax, kmin, kmax (kmax not clipped to the grid)
@@ -901,7 +907,7 @@ __global__ __launch_bounds__(DEPC_THREADS) void k_deposit_current(DepositArgs A)
             const double zp = (q[0] + h * q[6]) / dz, zm = (q[0] - h * q[6]) / dz;
             if (!z_on_grid(D, zp) || !z_on_grid(D, zm)) continue;
             const int lo = (int)floor(fmin(zp, zm)) - 1, hi = (int)floor(fmax(zp, zm)) + 2;
-            if (hi - lo + 1 > 8) {
+            if (hi - lo + 1 > 8 || !plain(q)) {
                 for (int p = p0; p < p0 + same; ++p) deposit_sample_wide<R>(A.eps, RXY, A.probs + p, (R *)A.j[p], q);
                 continue;
             }
@@ -918,7 +924,7 @@ __global__ __launch_bounds__(DEPC_THREADS) void k_deposit_current(DepositArgs A)
             }
         }
         block_minmax<DEPC_WAVES>(fp, red);
-        if (fp[1] < fp[0]) {  // nothing (or only wide samples) here
+        if (fp[1] < fp[0]) {  // nothing here, or only samples added by themselves
             p0 += same;
             continue;
         }
@@ -1066,7 +1072,7 @@ __global__ __launch_bounds__(DEPC_THREADS) void k_deposit_current(DepositArgs A)
                     const double z = q[0], x = q[1], y = q[2], qw = q[3], vx = q[4], vy = q[5], vz = q[6];
                     const double zc = z / dz, zp = (z + h * vz) / dz, zm = (z - h * vz) / dz;
                     const int lo = (int)floor(zc) - 1, l2 = (int)floor(fmin(zp, zm)) - 1, h2 = (int)floor(fmax(zp, zm)) + 2;
-                    const bool ok = z_on_grid(D, zp) && z_on_grid(D, zm) && h2 - l2 + 1 <= 8;
+                    const bool ok = z_on_grid(D, zp) && z_on_grid(D, zm) && h2 - l2 + 1 <= 8 && plain(q);
                     int b[3] = {0, 0, 0};
                     double cs[3], sn[3], vel[2] = {0.0, 0.0};
 #pragma unroll

@@ -72,6 +72,24 @@ def test_nan_position(kind, precision):
 
 
 @pytest.mark.parametrize("precision", [F.FP64, F.FP32C])
+@pytest.mark.parametrize("column,value,planes", [
+    (1, np.nan, {2, 3}),        # x: J_z and rho_xy at rows 0 .. 3 (J_rho, J_theta take no direction from it)
+    (4, np.nan, {0, 1, 2, 3}),  # v_x: the transverse currents at the sample too
+    (3, np.nan, {0, 1, 2, 3}),  # the weight: where the sample's shapes are
+])
+def test_nan_of_a_moving_sample_shows(column, value, planes, precision):
+    print(f"moving sample, column {column} {value}", flush=True)
+    s = ordinary(300, np.random.default_rng(5), True)
+    bad = np.array([[20.5 * DZ, 2 * DZ, DZ, 1.0, 0.2, 0.1, 0.5, 0.0]])
+    bad[0, column] = value
+    got, want = deposit("current", np.concatenate([s[:7], bad, s[7:]]), precision), deposit("current", s, precision)
+    nan = np.isnan(got)
+    assert {c for c in range(4) if nan[:, c].any()} == planes
+    assert not nan[:, :, 5:].any() and not nan[..., :18].any() and not nan[..., 25:].any()
+    assert rel_l2(np.where(nan, 0, got), np.where(nan, 0, want)) < (1e-12 if precision == F.FP64 else 1e-5)
+
+
+@pytest.mark.parametrize("precision", [F.FP64, F.FP32C])
 def test_nan_weight_of_a_fast_sample_stays_on_the_grid(precision):
     """More than 3 cells in a step, next to the axis: no row below the grid is added to."""
     s = ordinary(300, np.random.default_rng(7), True)
@@ -80,3 +98,11 @@ def test_nan_weight_of_a_fast_sample_stays_on_the_grid(precision):
     nan = np.isnan(got)
     assert nan[:, 0].any() and not nan[:, :, 5:].any() and not nan[..., :16].any() and not nan[..., 27:].any()
     assert rel_l2(np.where(nan, 0, got), np.where(nan, 0, want)) < (1e-12 if precision == F.FP64 else 1e-5)
+
+
+@pytest.mark.parametrize("precision", [F.FP64, F.FP32C])
+def test_infinite_weight_at_rest_leaves_the_transverse_currents(precision):
+    s = ordinary(300, np.random.default_rng(6), True)
+    bad = np.array([[20.5 * DZ, 2 * DZ, DZ, np.inf, 0.0, 0.0, 0.0, 0.0]])
+    got, want = deposit("current", np.concatenate([s[:7], bad, s[7:]]), precision), deposit("current", s, precision)
+    assert np.isfinite(got[:, :3]).all() and rel_l2(got[:, :3], want[:, :3]) < (1e-12 if precision == F.FP64 else 1e-5)
