@@ -1992,7 +1992,8 @@ __global__ __launch_bounds__(GATHER_BLOCK) __attribute__((amdgpu_waves_per_eu(4)
                 fp[1] = max(fp[1], i);
             }
         }
-        const double rc = (SS & 2) ? 2.0 * rho / A.dr : rho / A.dr - 0.5;
+        // (a rho beyond the range of int would wrap round to a row below the grid; 8 nodes beyond it is as good)
+        const double rc = fmin((SS & 2) ? 2.0 * rho / A.dr : rho / A.dr - 0.5, 2.0 * A.nr + 8.0);
         const int g0 = (int)floor(rc) - 1;
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
