@@ -29,6 +29,7 @@ constexpr int kEnvFuseND = 4;
 //   2900 x 360   72 | 61 40      75 | 66 55      77 | 69 60      79 | 76 70
 // (the waves of a small launch wait for the longest march, whatever it saves)
 constexpr size_t env_fuse_cells(int nd) { return nd <= 3 ? 1 << 19 : 700000; }
+constexpr int kEnvColumns = (1 << 27) - 1;  // widest grid: the bytes of a row are an int
 constexpr int kEnvRows = 640;  // most rows of a march (output rows, and the rows before and behind them)
 constexpr int env_depth(int nd) { return nd == 1 ? 4 : 2; }
 constexpr int env_out_columns(int nd) { return kEnvWaves * 32 - 2 * (env_depth(nd) - 1) * nd; }
@@ -56,6 +57,27 @@ FDETD_ENV_HD inline bool decode_fused(int nz, int nr, int r, int seg, int oc, Fu
     c.k0 = sl * seg;
     c.k1 = c.k0 + seg < nr ? c.k0 + seg : nr;
     return r >= 0 && c.o0 < nz && c.k0 < c.k1;
+}
+
+// Rows per segment for the `count` grids of a batch, and the tiles they give: a block marches the segment and the
+// rows before its first one, kEnvBlocks blocks at a time.  False where a group cannot take one of the grids.
+inline bool env_tiling(int nd, int count, const int *nz, const int *nr, int &seg, int &tiles)
+{
+    const int lag = (env_depth(nd) - 1) * nd, oc = env_out_columns(nd);
+    for (int t = 0; t < count; ++t)
+        if (nz[t] > kEnvColumns) return false;
+    long long least = -1;
+    for (int s = 8; s + 3 * lag + 4 <= kEnvRows; ++s) {
+        long long blocks = 0;
+        for (int t = 0; t < count; ++t) blocks += fused_tiles(nz[t], nr[t], s, oc);
+        const long long cost = (blocks + kEnvBlocks - 1) / kEnvBlocks * (s + 2 * lag + 4);
+        if (least < 0 || cost < least) {
+            least = cost;
+            seg = s;
+            tiles = (int)blocks;
+        }
+    }
+    return true;
 }
 
 }  // namespace fdetd

@@ -76,6 +76,7 @@ __device__ __forceinline__ void env_group(const EnvGroup &C, int o0, int k0, int
     CDesc &D = *C.D;
     const int nz = __builtin_amdgcn_readfirstlane(D.nz), nr = __builtin_amdgcn_readfirstlane(D.nr);
     const int lane = threadIdx.x % WAVE, strip = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+    static_assert((long long)kEnvColumns * SL * (int)sizeof(double) <= 0x7fffffff, "bytes of a row");
     const int rb = nz * SL * (int)sizeof(double), rbc = nz * (int)sizeof(double);
     const int base = max(0, k0 - (S - 1) * ND), niter = k1 - base + (S - 1) * ND;
     const int col = o0 - (S - 1) * ND + strip * G::CPW + lane / SL, ccol = min(max(col, 0), nz - 1);

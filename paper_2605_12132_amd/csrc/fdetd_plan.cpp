@@ -796,22 +796,17 @@ int plan_fused(fdetd_plan_t P, Batch &b, const ProbDesc *D)
     if (P->kind != FDETD_ENVELOPE || P->precision != FDETD_FP64 || b.nd < 1 || b.nd > kEnvFuseND || b.N % env_depth(b.nd))
         return FDETD_OK;
     size_t cells = 0;
-    for (int t = 0; t < b.count; ++t) cells += D[t].plane;
-    const int force = forced_env_fuse();
-    if (force == 0 || (force < 0 && cells < env_fuse_cells(b.nd))) return FDETD_OK;
-    // rows per segment: a block marches them and the rows before its first one, kEnvBlocks at a time
-    const int lag = (env_depth(b.nd) - 1) * b.nd, oc = env_out_columns(b.nd);
-    double least = 1e300;
-    for (int seg = 8; seg + 3 * lag + 4 <= kEnvRows; ++seg) {
-        int64_t blocks = 0;
-        for (int t = 0; t < b.count; ++t) blocks += fused_tiles(D[t].nz, D[t].nr, seg, oc);
-        const double cost = (double)((blocks + kEnvBlocks - 1) / kEnvBlocks) * (seg + 2 * lag + 4);
-        if (cost < least) {
-            least = cost;
-            b.fused_seg = seg;
-            b.fused = (int)blocks;
-        }
+    std::vector<int> nz(b.count), nr(b.count);
+    for (int t = 0; t < b.count; ++t) {
+        cells += D[t].plane;
+        nz[t] = D[t].nz;
+        nr[t] = D[t].nr;
     }
+    const int force = forced_env_fuse(), oc = env_out_columns(b.nd);
+    if (force == 0 || (force < 0 && cells < env_fuse_cells(b.nd))) return FDETD_OK;
+    int tiles = 0;
+    if (!env_tiling(b.nd, b.count, nz.data(), nr.data(), b.fused_seg, tiles)) return FDETD_OK;
+    b.fused = tiles;
     // the tiles cover the rows segment by segment, each from column 0 on without gap or overlap
     for (int t = 0; t < b.count; ++t) {
         int row = 0, col = 0;
