@@ -65,6 +65,7 @@ struct Batch {
     int tile_order = 0;        // numbering of the Maxwell tiles (ProbDesc::tile_order, autotuned)
     int fused = 0;             // envelope: tiles of the fused launch (0: stage by stage)
     int fused_seg = 0;         // ... and their rows
+    int fused_home = 0;        // ... also in a call's last step, where the state has to end in the caller's planes
     int lane = 0;              // stream of the batch's launches: 0 = the plan's stream, l > 0 = lanes[l - 1]
     double dt;
     std::vector<int> members;  // user indices, in table order
@@ -92,6 +93,7 @@ struct fdetd_plan_s {
     std::vector<int> seg_rows;  // per launch batch: rows per marching segment of the main launch
     std::vector<int> nt_store;  // per launch batch: store policy of the Maxwell stage outputs
     std::vector<int> tile_order;  // per launch batch: tile numbering
+    std::vector<int> fuse;  // per launch batch, timed: 0 stage by stage, 1 fused groups, 2 also in a call's last step
     // side streams of a plan whose launch batches run concurrently, with the fork and join events
     std::vector<hipStream_t> lanes;
     hipEvent_t fork_ev = nullptr;
@@ -495,7 +497,7 @@ int enqueue_envelope_batch(fdetd_plan_t P, const Batch &b, void *const *a, void 
 // and the state's next place.  step, n_steps: position in the call; the last step leaves the state with the caller:
 // where it starts there, its last group runs stage by stage, whose last stage works in place, or (a single group)
 // the result is copied back (one-step calls, 2900 x 360 and 6000 x 700, order 8: 79 and 355 us stage by
-// stage, 76 and 280 so).
+// stage, 76 and 280 so), or, where that is slower, the whole step runs stage by stage.
 int enqueue_envelope_fused(fdetd_plan_t P, const Batch &b, void *const *a, void *const *at, const void *const *chi,
                            int step, int n_steps, hipStream_t s)
 {
@@ -515,6 +517,7 @@ int enqueue_envelope_fused(fdetd_plan_t P, const Batch &b, void *const *a, void 
     A.sel_psi = moved ? 2 : 0;
     const int next = moved ? 0 : 2;
     const bool home = step == n_steps - 1 && !moved, tail = home && groups > 1;
+    if (home && !b.fused_home) return enqueue_envelope_batch(P, b, a, at, chi, s);
     int rc = damp_layers(P, b, a, at, moved, s);  // first factor exp(-sigma dt/4) of the split step
     if (rc) return rc;
     A.sel_in = A.sel_psi;
@@ -790,8 +793,9 @@ int forced_env_fuse()
     return -1;
 }
 
-// Whether batch b's envelope steps (problems D[0 .. b.count)) run in fused groups of stages, and their tiles.
-int plan_fused(fdetd_plan_t P, Batch &b, const ProbDesc *D)
+// Whether batch b's envelope steps (problems D[0 .. b.count)) run in fused groups of stages, and their tiles.  fuse:
+// as timed (tune_fused), -1 without timing.
+int plan_fused(fdetd_plan_t P, Batch &b, const ProbDesc *D, int fuse)
 {
     if (P->kind != FDETD_ENVELOPE || P->precision != FDETD_FP64 || b.nd < 1 || b.nd > kEnvFuseND || b.N % env_depth(b.nd))
         return FDETD_OK;
@@ -806,6 +810,17 @@ int plan_fused(fdetd_plan_t P, Batch &b, const ProbDesc *D)
     if (force == 0 || (force < 0 && cells < env_fuse_cells(b.nd))) return FDETD_OK;
     int tiles = 0;
     if (!env_tiling(b.nd, b.count, nz.data(), nr.data(), b.fused_seg, tiles)) return FDETD_OK;
+    // Untimed plans: not where the blocks' columns lie beside the grids for the most part, and the copies that end a
+    // step of one group only for large grids.  us per step of 4 stages one by one | fused, one group and its copies:
+    // 128 x 4687 (two blocks wide, 53 % in the grid) order 6 54 | 59, order 8 57 | 63, order 2 51 | 60; 20 x 50000
+    // order 8 92 | 144; 200 x 5000 (83 %) order 6 78 | 72, order 8 84 | 77, order 2 75 | 62; 40 grids of 64 x 256,
+    // order 2, one step 83 | 275.
+    double formed = 0.0;
+    for (int t = 0; t < b.count; ++t) formed += (double)nr[t] * ((nz[t] + oc - 1) / oc) * oc;
+    if (force < 0 && (fuse < 0 ? formed > 1.45 * cells : fuse == 0)) return FDETD_OK;
+    if (force > 0) fuse = 2;
+    if (fuse < 0) fuse = b.N > env_depth(b.nd) || cells >= (size_t)b.count << 20 ? 2 : 1;
+    b.fused_home = fuse == 2;
     b.fused = tiles;
     // the tiles cover the rows segment by segment, each from column 0 on without gap or overlap
     for (int t = 0; t < b.count; ++t) {
@@ -903,7 +918,7 @@ int build_batches(fdetd_plan_t P)
         b.ntiles = tiles;
         b.ntiles_ax = tiles_ax;
         if (!store_policy_applies(P, b)) b.nt_store = 0;
-        if (int rc = plan_fused(P, b, P->desc.data() + b.d0)) return rc;
+        if (int rc = plan_fused(P, b, P->desc.data() + b.d0, bi < P->fuse.size() ? P->fuse[bi] : -1)) return rc;
         P->batches.push_back(b);
         t = u;
     }
@@ -981,6 +996,65 @@ BatchArgs tuning_args(fdetd_plan_t P, const Batch &b, const std::vector<void *> 
         A.chi[t] = base + np * pb;
     }
     return A;
+}
+
+// Times the envelope steps of the batches that could run in fused groups, at their tuned segment length: stage by
+// stage, fused as in the middle of a call, and as a call of one step.  What a group saves depends on the shapes (the
+// share of a block's columns that lie in the grid, rows per segment, problems per copy); only timing tells.  The state
+// stands in scratch[p] (a, a_tilde, chi; zeros), ev: two events.
+int tune_fused(fdetd_plan_t P, const std::vector<void *> &scratch, hipEvent_t *ev, bool log)
+{
+    const size_t nb = P->batches.size(), eb = elem_bytes(P->precision);
+    P->fuse.assign(nb, 2);
+    if (int rc = build_batches(P)) return rc;
+    if (std::none_of(P->batches.begin(), P->batches.end(), [](const Batch &b) { return b.fused > 0; })) return FDETD_OK;
+    std::vector<int> best(nb, 0);
+    std::vector<void *> a(P->probs.size()), at(P->probs.size());
+    std::vector<const void *> chi(P->probs.size());
+    for (size_t p = 0; p < P->probs.size(); ++p) {
+        const size_t pb = P->probs[p].cells * eb;
+        a[p] = scratch[p];
+        at[p] = (char *)scratch[p] + pb;
+        chi[p] = (char *)scratch[p] + 2 * pb;
+    }
+    struct Flags {  // no events around the stages timed here
+        fdetd_plan_t P;
+        uint32_t f;
+        ~Flags() { P->flags = f; }
+    } flags{P, P->flags};
+    P->flags &= ~FDETD_PLAN_PROFILE;
+    for (size_t bi = 0; bi < nb; ++bi) {
+        const Batch &b = P->batches[bi];
+        if (!b.fused) continue;
+        auto two_steps = [&](int how) -> int {
+            for (int st = 0; st < 2; ++st) {
+                const int rc = how == 0 ? enqueue_envelope_batch(P, b, a.data(), at.data(), chi.data(), P->stream)
+                                        : enqueue_envelope_fused(P, b, a.data(), at.data(), chi.data(), how == 1 ? st : 0,
+                                                                 how == 1 ? 2 : 1, P->stream);
+                if (rc) return rc;
+            }
+            return FDETD_OK;
+        };
+        double t[3] = {1e300, 1e300, 1e300};
+        if (int rc = two_steps(0)) return rc;  // untimed
+        for (int pass = 0; pass < 2; ++pass)  // in opposite orders, keeping each one's faster time
+            for (int k = 0; k < 3; ++k) {
+                const int how = pass == 0 ? k : 2 - k;
+                float ms = 0.f;
+                HIPCHK(P, hipEventRecord(ev[0], P->stream));
+                if (int rc = two_steps(how)) return rc;
+                HIPCHK(P, hipEventRecord(ev[1], P->stream));
+                HIPCHK(P, hipEventSynchronize(ev[1]));
+                HIPCHK(P, hipEventElapsedTime(&ms, ev[0], ev[1]));
+                t[how] = std::min(t[how], (double)ms / 2);
+            }
+        best[bi] = t[1] >= t[0] ? 0 : t[2] < t[0] ? 2 : 1;
+        if (log)
+            std::fprintf(stderr, "fdetd autotune batch %zu envelope step: %.4f ms stage by stage, %.4f fused, %.4f fused "
+                         "as a call of one step -> %d\n", bi, t[0], t[1], t[2], best[bi]);
+    }
+    P->fuse = best;
+    return build_batches(P);
 }
 
 // Plan-time autotuning of the marching segment length: each launch batch runs a few timed stages at every
@@ -1082,6 +1156,7 @@ int autotune(fdetd_plan_t P, double &ms_spent)
         P->seg_rows = best;
         rc = build_batches(P);
     }
+    if (!rc && P->kind == FDETD_ENVELOPE && forced_env_fuse() < 0) rc = tune_fused(P, scratch, ev, log);
     // Store policy of the stage outputs and numbering of the tiles, at the chosen segment length: pairs of
     // consecutive stages (N - 2 and N - 3, each reading the other's output as in a step) under each of the
     // four combinations, two passes in opposite orders, the fastest kept.  Non-temporal outputs pay on grids
