@@ -119,9 +119,12 @@ typedef struct {
     double dt_rho_max;        /* max over problems of dt * estimated spectral radius of H (0: skipped) */
     double stability_margin;  /* min over problems of X_N / (dt * rho_hat) (0: skipped)                */
     int64_t cells;            /* sum over problems of nz * nr                                      */
-    int64_t bytes_per_step;   /* algorithmic HBM bytes of one step of all problems                 */
+    int64_t bytes_per_step;   /* algorithmic HBM bytes of one step of all problems (as launches_per_step) */
     int64_t scratch_bytes;    /* device memory owned by the plan                                  */
-    int64_t launches_per_step;
+    int64_t launches_per_step;  /* of a step inside a call.  An envelope plan that runs several stages per
+                                   launch takes more in a call's last step where an even number of steps
+                                   comes before it: that step's last launch, or the step, runs stage by
+                                   stage, or two copies per problem bring the state back                  */
     /* FDETD_PLAN_PROFILE: stage kernels timed since the previous fdetd_query (query synchronises) */
     int64_t profiled_launches;
     double profiled_ms;          /* sum of their durations                                       */

@@ -21,7 +21,8 @@ namespace fdetd {
 constexpr int kEnvWaves = 4;
 constexpr int kEnvBlocks = 512;           // blocks that run at a time: two per CU
 constexpr int kEnvFuseND = 4;
-// Fewest cells of a launch that takes groups, or (autotuned plans) times them against the single stages.  us per step of 4 stages one by one | fused, in calls of 1 and of 2 steps:
+// Fewest cells of a launch that takes groups, or (autotuned plans) times them against the single stages.  us per
+// step of 4 stages one by one | fused, in calls of 1 and of 2 steps:
 //                  order 2         order 4         order 6         order 8
 //   1400 x 180   30 | 35 27      32 | 32 32      32 | 37 38      34 | 38 41
 //   2048 x 256   44 | 44 29      45 | 43 41      46 | 45 43      48 | 50 52

@@ -1570,6 +1570,12 @@ int fdetd_plan(const fdetd_problem_desc *probs, int32_t n_probs, int32_t precisi
     P->info.dt_rho_max = worst;
     P->info.stability_margin = margin;
     P->info.cells = cells;
+    for (const Batch &b : P->batches)  // groups read and write as a stage does, once for all their stages
+        if (b.fused)
+            for (const int p : b.members) {
+                const int64_t c = (int64_t)(P->probs[p].cells * eb);
+                bytes_step += (c * 13 / 2) * (b.N / env_depth(b.nd) - b.N) - 2 * c;
+            }
     P->info.bytes_per_step = bytes_step;
     P->info.scratch_bytes = scratch;
     for (const Batch &b : P->batches) {  // Maxwell: N stages (two launches each when a batch that mixes

@@ -53,3 +53,22 @@ def test_every_route_gives_the_same_bits(monkeypatch, nz, nr, order, steps):
     for flags in (1, 3, 1 | F.PLAN_NO_AUTOTUNE):
         ga, gt, _ = gpu_envelope(w, a, at, chi, steps, flags=flags)
         assert all(np.array_equal(x, y) for x, y in zip(ga + gt, sa + st))
+
+
+@pytest.mark.parametrize("order,N", [(2, 4), (2, 8), (8, 4), (6, 6)])
+def test_query_counts_what_runs(monkeypatch, order, N):
+    """bytes_per_step and launches_per_step of grouped steps: 4.5 complex values per cell for the first group and 6.5
+    for each further one, as the profiled launches of a call of two steps are counted."""
+    import torch
+    monkeypatch.setenv("FDETD_ENV_FUSE", "1")
+    nz, nr, groups = 250, 60, N // (4 if order == 2 else 2)
+    plan = F.Plan([F.Problem(nz, nr, 0, order, N, DZ, 0.2 * I.UM, 0.5 * DZ, k0=1.0, kind=F.ENVELOPE)], precision=F.FP64,
+                  flags=F.PLAN_SKIP_STABILITY | F.PLAN_PROFILE)
+    planes = [torch.zeros((nr, nz), dtype=torch.complex128, device="cuda") for _ in range(2)]
+    plan.envelope_step(planes[:1], planes[1:], [torch.zeros((nr, nz), dtype=torch.float64, device="cuda")], n_steps=2)
+    torch.cuda.synchronize()
+    info = plan.query()
+    plan.close()
+    assert info["launches_per_step"] == groups
+    assert info["bytes_per_step"] == nz * nr * 16 * (6.5 * groups - 2)
+    assert info["profiled_launches"] == 2 * groups and info["profiled_bytes"] == 2 * info["bytes_per_step"]
