@@ -701,7 +701,7 @@ def main():
     log(f"FP64 stage kernel: {roof64['avg_launch_us']} us/launch, {roof64['achieved']} GB/s ({roof64['frac'] * 100:.1f}% of HBM)")
     psi32, ms32, t32, info32 = run_graph_path(w, F.FP32C, K, W, jg, args.seg_rows_fp32c)
     rate32 = cells * K / (ms32 * 1e-3)
-    roof32 = profile_pass(w, F.FP32C, args.profile_steps, jg, info32["seg_rows"], info32["seg_rows_axis"],
+    roof32 = profile_pass(w, F.FP32C, args.profile_steps, jg, info32["seg_rows"], info32["tile_rows_axis"],
                           info32["store_policy"], info32["tile_order"])
     errs = fp32c_errors(w, psi64, psi32)
     del psi32

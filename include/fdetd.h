@@ -130,8 +130,8 @@ typedef struct {
     double profiled_ms;          /* sum of their durations                                       */
     double profiled_bytes;       /* sum of their algorithmic HBM bytes                           */
     /* tiling of the first launch batch: rho rows per marching segment of the main launch and of the
-     * FP32C near-axis launch (0 without one; small launches share a near-axis segment out over up to 4
-     * wavefronts), and the plan-time autotuning that picked them (0 ms: none) */
+     * FP32C near-axis launch (0 without one; small plans share a near-axis segment out over up to 4
+     * wavefronts, see tile_rows_axis), and the plan-time autotuning that picked them (0 ms: none) */
     int32_t seg_rows, seg_rows_axis;
     double autotune_ms;
     int32_t streams;  /* streams a step call runs on: 1, or up to 4 when the plan has several launch batches */
@@ -141,6 +141,8 @@ typedef struct {
                               the increment form)                                                   */
     int32_t tile_order;    /* numbering of the Maxwell tiles of the first launch batch: 0 half, segment,
                               strip; 1 segment, half, strip (timed at plan time; FDETD_TILE_ORDER fixes it) */
+    int32_t tile_rows_axis;  /* rows that one wavefront of the near-axis launch marches: seg_rows_axis, or a
+                                half or a quarter of 16 in small plans                                */
 } fdetd_plan_info;
 
 /* Build a plan for n_probs problems (all FDETD_MAXWELL or all FDETD_ENVELOPE).

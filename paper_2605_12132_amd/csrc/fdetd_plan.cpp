@@ -1589,6 +1589,7 @@ int fdetd_plan(const fdetd_problem_desc *probs, int32_t n_probs, int32_t precisi
     P->info.launches_per_step = launches;
     P->info.seg_rows = P->batches.empty() ? 0 : P->batches[0].seg;
     P->info.seg_rows_axis = P->desc.empty() ? 0 : std::min(axis_segment_rows(), P->desc[0].ax_rows);
+    P->info.tile_rows_axis = P->desc.empty() || !P->desc[0].ax_rows ? 0 : P->desc[0].seg_ax;
     P->info.store_policy = P->batches.empty() ? 0 : P->batches[0].nt_store;
     P->info.tile_order = P->batches.empty() ? 0 : P->batches[0].tile_order;
     P->info.autotune_ms = tune_ms;
