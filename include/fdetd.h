@@ -96,6 +96,8 @@ extern "C" {
  *   FDETD_STORE_POLICY  0 or 1: Maxwell stage outputs stored with the default or non-temporal cache policy
  *                       (otherwise timed at plan time with the segment length)
  *   FDETD_TILE_ORDER    0 or 1: Maxwell tiles numbered half first or segment first (otherwise timed)
+ *   FDETD_ENV_FUSE      0 or 1: FP64 envelope steps stage by stage, or in groups of stages wherever N_D and N allow
+ *                       them (otherwise timed, see launches_per_step)
  *   FDETD_AUTOTUNE_LOG  set: the tuning's per-candidate times on stderr
  * and one that changes FP32C results, for measuring what the FP64 near-axis band buys:
  *   FDETD_AXIS_ROWS     0..4096: rows next to the axis that FP32C plans compute in FP64 (default 2 N_D) */
