@@ -34,8 +34,8 @@ constexpr int kEnvColumns = (1 << 27) - 1;  // widest grid: the bytes of a row a
 constexpr int kEnvRows = 640;  // most rows of a march (output rows, and the rows before and behind them)
 constexpr int env_depth(int nd) { return nd == 1 ? 4 : 2; }
 constexpr int env_out_columns(int nd) { return kEnvWaves * 32 - 2 * (env_depth(nd) - 1) * nd; }
-// Arguments of a group's launch: those of a stage (psi, aux, chi: the caller's planes) with role = ROLE_ENV_GROUP, by
-// which the stage launch hands them on, and
+// Arguments of a group's launch: those of a stage (psi, aux, chi: the caller's planes) and more.  The FP64 stage
+// launches of fdetd_march.hip hand them on to launch_envelope_fused by their role.
 constexpr int ROLE_ENV_GROUP = 3;
 struct EnvFuseArgs : BatchArgs {
     int seg;                       // rows per segment
@@ -43,6 +43,7 @@ struct EnvFuseArgs : BatchArgs {
     double coefs[4];               // of the group's stages, in order
     int begin[kMaxBatch];          // first tile of each problem
 };
+hipError_t launch_envelope_group(int nd, EnvFuseArgs a, hipStream_t s);  // dispatch on nd (fdetd_dispatch.cpp)
 hipError_t launch_envelope_fused(int nd, const EnvFuseArgs &a, hipStream_t s);
 
 // A tile: first output column, output rows.  Tile r of an nz x nr grid: oc output columns per tile, seg rows per

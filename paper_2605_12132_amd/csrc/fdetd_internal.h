@@ -127,7 +127,8 @@ struct BatchArgs {
     int has_src, compensated;
     // FP32C increment form (Maxwell): the stage vector is the increment d = v - psi, and stage n writes
     // d_n = beta_n Jbar + coef (P + H d_{n+1}) with P = H psi formed once per step (role 1: P = H psi_lo
-    // from zero, role 2: P += H psi_hi; role 0: a Horner stage), the last stage TwoSum(psi_hi, lo + d_0)
+    // from zero, role 2: P += H psi_hi; role 0: a Horner stage), the last stage TwoSum(psi_hi, lo + d_0).
+    // Role 3 (ROLE_ENV_GROUP): the base of an EnvFuseArgs, set by launch_envelope_group alone
     int increment, role;
     // the first stage with a current forms the E part of w_N from psi and Jbar as it loads them (no
     // k_form_wn pass before it): the Horner form, not the compensated N = 1 stage

@@ -1189,7 +1189,8 @@ hipError_t go_maxwell_any_v(const BatchArgs &a, hipStream_t s)
     template <>                                                                                      \
     hipError_t march_envelope_nd<N>(int prec, const BatchArgs &a, hipStream_t s)                     \
     {                                                                                                \
-        if (a.role == ROLE_ENV_GROUP) return launch_envelope_fused(N, static_cast<const EnvFuseArgs &>(a), s); \
+        if (a.role == ROLE_ENV_GROUP)                                                                \
+            return prec == P64 ? launch_envelope_fused(N, static_cast<const EnvFuseArgs &>(a), s) : hipErrorInvalidValue; \
         return prec == P64 ? go_envelope<double2, N>(a, s) : go_envelope<float2, N>(a, s);           \
     }                                                                                                \
     template <>                                                                                      \

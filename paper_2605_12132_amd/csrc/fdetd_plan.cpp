@@ -505,7 +505,6 @@ int enqueue_envelope_fused(fdetd_plan_t P, const Batch &b, void *const *a, void 
     const int depth = env_depth(b.nd), groups = b.N / depth;
     EnvFuseArgs A{};
     const size_t cells = envelope_args(P, b, a, at, chi, A);
-    A.role = ROLE_ENV_GROUP;
     A.ntiles = b.fused;
     A.seg = b.fused_seg;
     for (int t = 0, begin = 0; t < b.count; ++t) {
@@ -532,7 +531,7 @@ int enqueue_envelope_fused(fdetd_plan_t P, const Batch &b, void *const *a, void 
         for (int t = 0; t < depth; ++t) A.coefs[t] = b.dt / (b.N - g * depth - t);
         // algorithmic bytes: vin (2c) + psi (2c; the same data in the first group) + chi + out (2c)
         if ((rc = profile_begin(P, ((g == 0 ? 4.0 : 6.0) + 0.5) * cells * eb))) return rc;
-        HIPCHK(P, launch_envelope_march(P64, b.nd, A, s));
+        HIPCHK(P, launch_envelope_group(b.nd, A, s));
         if ((rc = profile_end(P))) return rc;
         A.sel_in = A.sel_out;
     }
