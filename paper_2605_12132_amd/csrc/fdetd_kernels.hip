@@ -1808,8 +1808,8 @@ __global__ __launch_bounds__(256) void k_destagger(DestaggerArgs A)
 // other's arithmetic.  A sample reads 16 nodes of each of the 6 planes of every mode, so the block first copies
 // the nodes and rows its samples' shapes touch (rows below the axis read rows 0 and 1) into an LDS tile of
 // GATHER_TILE values (as FP64): all planes at once where they fit -- position-ordered samples make the
-// footprint small -- else as many planes per pass as do.  Only a footprint beyond the tile by itself is read
-// from the planes directly, where the scattered 16-byte reads bound the kernel: a bunch 100 rows wide, whose
+// footprint small -- else as many planes per pass as do.  Read from the planes directly (footprints beyond the
+// tile, or too wide for few samples) the scattered 16-byte reads bound the kernel: a bunch 100 rows wide, whose
 // 18 planes do not fit together (10^6 samples, three modes of a 4096 x 512 grid, FP64), took 537 us that way and
 // takes 190 us in four passes.
 constexpr int GATHER_BLOCK = 512, GATHER_TILE = 4096;
@@ -1846,10 +1846,24 @@ __global__ __launch_bounds__(GATHER_BLOCK) __attribute__((amdgpu_waves_per_eu(4)
     // groups of 16-byte reads, and the lanes of a wave (samples at about the same z) differ mostly in row.
     const bool any = fp[1] >= fp[0] && fp[3] >= fp[2];  // some sample of the block touches the grid
     const int tz = any ? fp[1] - fp[0] + 1 : 0, tr = any ? fp[3] - fp[2] + 1 : 0, ts = tz | 1;
-    // planes copied per pass: all of them where they fit, else as many as do (0: none, the samples read the
-    // planes directly)
     const int64_t per_plane = (int64_t)ts * tr;
-    const int npl = 6 * A.nprob, fit = any ? (int)(per_plane * npl <= GATHER_TILE ? npl : GATHER_TILE / per_plane) : 0;
+    const int64_t rest = A.n - (int64_t)blockIdx.x * GATHER_BLOCK;
+    const int npl = 6 * A.nprob, mine = rest < GATHER_BLOCK ? (int)rest : GATHER_BLOCK;  // planes, the block's samples
+    // Planes copied per pass: all of them where they fit, else as many as do, where that repays the copies (0: the
+    // samples read the planes directly).  A pass is two waits of the whole block, its copies grow with the footprint
+    // and what they save grows with the samples; the direct reads of FP32 planes are the cheaper ones until the blocks
+    // fill the chip.  us direct | in passes, three modes, footprints of 33 x 33, 43 x 43 and 62 x 63 values:
+    //   FP64  n =    40    37 | 39     38 |        38 | 69          FP32  n =    40    56 | 44     56 | 55     57 | 78
+    //   FP64  n =   300    54 | 48     57 | 57     63 | 82          FP32  n =   300    58 | 53     59 | 61     60 | 91
+    //   FP64  n =   512    72 | 51     75 | 60     88 | 85          FP32  n =   512    72 | 56     71 | 65     77 | 94
+    //   FP64  n =  5000    78 | 59     89 | 68    123 | 104         FP32  n =  5000    73 | 57     73 | 66     80 | 97
+    //   FP64  n = 3 10^5  176 | 112   183 | 126   224 | 195         FP32  n = 3 10^5  177 | 109   181 | 124   202 | 174
+    const bool full = mine == GATHER_BLOCK;
+    int fit = 0;
+    if (any && per_plane * npl <= GATHER_TILE) fit = npl;
+    else if (any && per_plane <= (sizeof(R) == 8 ? (full ? GATHER_TILE : 6 * mine)
+                                                 : (gridDim.x >= 256 ? GATHER_TILE : full ? 2048 : 1400)))
+        fit = (int)(GATHER_TILE / per_plane);
     const bool use_tile = fit > 0;  // uniform
     // e^(i theta) from the position itself (theta = 0 on the axis); e^(i m theta) is its m-th power
     const double c1 = rho > 0.0 ? x / rho : 1.0, s1 = rho > 0.0 ? y / rho : 0.0;
@@ -1872,37 +1886,46 @@ __global__ __launch_bounds__(GATHER_BLOCK) __attribute__((amdgpu_waves_per_eu(4)
         row[v] = min(max(q, rlo), rhi) - rlo;
         below[v] = k < 0;
     }
-    // the planes in order of mode, then component; cr + i ci = e^(i m theta) of the current mode
-    double acc[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0}, cr = 1.0, ci = 0.0;
+    // The planes in order of component, then mode: a component's sum goes on from one pass to the next (mode by mode
+    // all six went on, and 3 10^5 samples in one cell, three modes, took 79 us instead of 70).
+    // cr + i ci = e^(i mp theta).
+    double acc = 0.0, cr = 1.0, ci = 0.0;
+    int mp = 0;
+    const int inv = __builtin_amdgcn_readfirstlane((65536 + A.nprob - 1) / A.nprob);
+    // q / nprob for q < 6 nprob, nprob <= kMaxGather = 16 (a division per plane cost 2 % of the kernel)
+    auto component = [&](int q) { return q * inv >> 16; };
     const int step = use_tile ? fit : npl;
 #pragma unroll 1
     for (int q0 = 0; q0 < npl; q0 += step) {
         const int q1 = min(npl, q0 + step);
         if (use_tile) {
             if (q0) __syncthreads();  // the last pass's reads are done
-            for (int q = q0; q < q1; ++q) {
-                const V *f = (const V *)A.plane[q / 6][q % 6] + (size_t)fp[2] * A.nz + fp[0];
-                for (int e = threadIdx.x; e < tz * tr; e += GATHER_BLOCK) {
-                    const int k = e / tz, i = e % tz;
-                    const V v = f[(size_t)k * A.nz + i];
-                    tile[((q - q0) * tr + k) * ts + i] = double2{(double)v.x, (double)v.y};
-                }
-            }
+            const int per = tz * tr;
+            auto copy = [&](int q, int cell) {
+                const int k = cell / tz, i = cell % tz;
+                const V v = ((const V *)A.plane[q - component(q) * A.nprob][component(q)])[(size_t)(fp[2] + k) * A.nz + fp[0] + i];
+                tile[((q - q0) * tr + k) * ts + i] = double2{(double)v.x, (double)v.y};
+            };
+            if (fit == npl)  // small planes: the block's threads over all of them at once
+                for (int e = threadIdx.x; e < per * npl; e += GATHER_BLOCK) copy(e / per, e % per);
+            else
+                for (int q = q0; q < q1; ++q)
+                    for (int e = threadIdx.x; e < per; e += GATHER_BLOCK) copy(q, e);
             __syncthreads();
         }
         if (!live) continue;
 #pragma unroll 1
         for (int q = q0; q < q1; ++q) {
-            const int p = q / 6, c = q % 6, m = A.m[p];
-            if (c == 0) {
+            const int c = component(q), p = q - c * A.nprob, m = A.m[p];
+            if (m < mp) {  // else on from the mode before
                 cr = 1.0;
                 ci = 0.0;
-                for (int j = 0; j < (m < 0 ? -m : m); ++j) {
-                    const double t = cr * c1 - ci * s1;
-                    ci = cr * s1 + ci * c1;
-                    cr = t;
-                }
-                if (m < 0) ci = -ci;
+                mp = 0;
+            }
+            for (; mp < m; ++mp) {
+                const double t = cr * c1 - ci * s1;
+                ci = cr * s1 + ci * c1;
+                cr = t;
             }
             const double pS = (m % 2 == 0) ? 1.0 : -1.0, pA = ((m > 1 ? m - 1 : 1 - m) % 2 == 0) ? 1.0 : -1.0;
             const double par = (c == 2 || c == 5) ? pS : pA;
@@ -1937,14 +1960,13 @@ __global__ __launch_bounds__(GATHER_BLOCK) __attribute__((amdgpu_waves_per_eu(4)
                 re += wa * rre;
                 im += wa * rim;
             }
-            const double val = re * cr - im * ci;
-#pragma unroll
-            for (int u = 0; u < 6; ++u) acc[u] += u == c ? val : 0.0;
+            acc += re * cr - im * ci;
+            if (p == A.nprob - 1) {
+                A.fields[6 * s + c] = acc;
+                acc = 0.0;
+            }
         }
     }
-    if (!live) return;
-#pragma unroll
-    for (int c = 0; c < 6; ++c) A.fields[6 * s + c] = acc[c];
 }
 
 // Interpolation on the doubled grid (2x supersampling, section 3.4; SS bit 0: z, bit 1: rho), one thread
