@@ -1415,23 +1415,36 @@ __device__ __forceinline__ double2 ld2(const V *p, size_t q)
     return double2{(double)v.x, (double)v.y};
 }
 
-// A block of CORR_COLS columns and CORR_ROWS rows holds the stencil's operand, CORR_ROWS + 2 N_D - 1 rows of it, in
-// LDS, so that a value is read and scaled once per block instead of 2 N_D times: reads from the L2 bounded it
-// (2048 x 256, order 16, FP64: 15.1 us, now 10.4 at 4.1 TB/s of what it has to move).  The same tile left k_corr_apply,
-// which reads two and writes two planes beside its operand, where it was (11.2 and 11.0 us).
-constexpr int CORR_COLS = 64, CORR_ROWS = 16, CORR_WAVES = 4;
+// A block of CORR_COLS columns and ROWS rows holds the stencil's operand, ROWS + 2 N_D - 1 rows of it, in LDS, so that
+// a value is read and scaled once per block instead of 2 N_D times: reads from the L2 bounded it (2048 x 256, order 16,
+// FP64: 15.1 us, now 9.7 at 4.4 TB/s of what it has to move).  The same tile left k_corr_apply, which reads two and
+// writes two planes beside its operand, where it was (11.2 and 11.0 us).  Rows per block: small grids need the blocks,
+// and each wavefront its loads in one go.  us per step of two modes (N = 2) without a tile | 4, 8, 16 rows:
+//    257 x 33,  order 2  FP64  58 |  58  59  62     FP32C  60 |  61  62  65
+//    611 x 149, order 4        91 |  89  91  93            87 |  86  88  90
+//   5000 x 20,  order 8        94 |  91  92  96            85 |  85  87  90
+//   1024 x 1024, order 32     754 | 725 719 725           665 | 637 629 634
+constexpr int CORR_COLS = 64, CORR_WAVES = 4;
 
 // d(k, i) = rho_xy - rho_k^-1 sum_j a_j (g(k + j) - g(k - j + 1)) / dr - (i m / rho_k) J_theta,
 // g(q) = q dr Jbar_rho(q) on the staggered rows, 0 on the axis, parity * g(-q) below it, 0 from nr on.
-template <typename R>
+template <typename R, int ROWS>
 __global__ __launch_bounds__(CORR_WAVES *CORR_COLS) void k_corr_div(CorrectArgs A)
 {
     using V = typename cplx_of<R>::V;
     extern __shared__ double2 tile[];  // row t: g(k0 - N_D + 1 + t)
-    const int c = threadIdx.x % CORR_COLS, w = threadIdx.x / CORR_COLS, k0 = blockIdx.y * CORR_ROWS, nd = A.nd;
+    const int c = threadIdx.x % CORR_COLS, w = threadIdx.x / CORR_COLS, k0 = blockIdx.y * ROWS, nd = A.nd;
     const int i = blockIdx.x * CORR_COLS + c, ic = min(i, A.nz - 1);
     const V *jr = (const V *)A.jbar;
-    for (int t = w; t < CORR_ROWS + 2 * nd - 1; t += CORR_WAVES) {
+    // the other operands are under way while the tile fills
+    double2 jt[ROWS / CORR_WAVES], rx[ROWS / CORR_WAVES];
+#pragma unroll
+    for (int u = 0; u < ROWS / CORR_WAVES; ++u) {
+        const size_t o = (size_t)min(k0 + w + u * CORR_WAVES, A.nr - 1) * A.nz + ic;
+        jt[u] = ld2((const V *)A.jth_in, o);
+        rx[u] = ld2((const V *)A.rho_xy, o);
+    }
+    for (int t = w; t < ROWS + 2 * nd - 1; t += CORR_WAVES) {
         const int q = k0 - nd + 1 + t, qq = q < 0 ? -q : q;
         const double2 v = ld2(jr, (size_t)min(qq, A.nr - 1) * A.nz + ic);
         const double f = q == 0 || qq >= A.nr ? 0.0 : (q < 0 ? (double)A.parity : 1.0) * qq * A.dr;
@@ -1439,8 +1452,10 @@ __global__ __launch_bounds__(CORR_WAVES *CORR_COLS) void k_corr_div(CorrectArgs 
     }
     __syncthreads();
     if (i >= A.nz) return;
-    for (int r = w; r < CORR_ROWS && k0 + r < A.nr; r += CORR_WAVES) {
-        const int k = k0 + r;
+#pragma unroll
+    for (int u = 0; u < ROWS / CORR_WAVES; ++u) {
+        const int r = w + u * CORR_WAVES, k = k0 + r;
+        if (k >= A.nr) return;
         const double2 *g = tile + (r + nd - 1) * CORR_COLS + c;  // g(k)
         double sx = 0.0, sy = 0.0;
 #pragma unroll 4
@@ -1450,11 +1465,9 @@ __global__ __launch_bounds__(CORR_WAVES *CORR_COLS) void k_corr_div(CorrectArgs 
             sy += A.a[j - 1] * (p.y - q.y);
         }
         const double rho = (k + 0.5) * A.dr;
-        const size_t o = (size_t)k * A.nz + i;
-        const double2 t = ld2((const V *)A.jth_in, o), d = ld2((const V *)A.rho_xy, o);
         const double mr = A.m / rho;
         // (i m / rho) (tx + i ty) = (-mr ty, mr tx)
-        A.work[o] = double2{d.x - sx / (A.dr * rho) + mr * t.y, d.y - sy / (A.dr * rho) - mr * t.x};
+        A.work[(size_t)k * A.nz + i] = double2{rx[u].x - sx / (A.dr * rho) + mr * jt[u].y, rx[u].y - sy / (A.dr * rho) - mr * jt[u].x};
     }
 }
 
@@ -2208,11 +2221,14 @@ hipError_t launch_ponderomotive(int prec, const ProbDesc *d, int nz, int nr, int
 
 hipError_t launch_correct_div(int prec, const CorrectArgs &a, hipStream_t s)
 {
-    const dim3 grid((unsigned)((a.nz + CORR_COLS - 1) / CORR_COLS), (unsigned)((a.nr + CORR_ROWS - 1) / CORR_ROWS));
-    const dim3 block(CORR_WAVES * CORR_COLS);
-    const unsigned lds = (CORR_ROWS + 2 * a.nd - 1) * CORR_COLS * sizeof(double2);  // 48128 bytes at N_D = 16
-    if (prec == P64) hipLaunchKernelGGL(k_corr_div<double>, grid, block, lds, s, a);
-    else hipLaunchKernelGGL(k_corr_div<float>, grid, block, lds, s, a);
+    auto go = [&](auto kernel, int rows) {
+        const dim3 grid((unsigned)((a.nz + CORR_COLS - 1) / CORR_COLS), (unsigned)((a.nr + rows - 1) / rows));
+        const unsigned lds = (rows + 2 * a.nd - 1) * CORR_COLS * sizeof(double2);  // 39936 bytes of 8 rows at N_D = 16
+        hipLaunchKernelGGL(kernel, grid, dim3(CORR_WAVES * CORR_COLS), lds, s, a);
+    };
+    const bool small = (int64_t)a.nz * a.nr < 1 << 19;
+    if (prec == P64) small ? go(k_corr_div<double, 4>, 4) : go(k_corr_div<double, 8>, 8);
+    else small ? go(k_corr_div<float, 4>, 4) : go(k_corr_div<float, 8>, 8);
     return hipGetLastError();
 }
 
