@@ -774,14 +774,19 @@ int axis_segment_rows()
 //            2048 x 256, 1 mode   179 153 177 | 216 245 233                 3000 x 300       83 65 62 | 102 81 83
 //            1531 x 203, 2 modes  204 196 186 | 266 251 261                 2048 x 256, two  85 69 68 | 105 90 85
 //            3000 x 300, 1 mode   236 237 241 | 283 309 333                 3000 x 300, two 101 97 99 | 128 132 130
-// (order 8, whose band is one segment of 8 rows: alike).
+// (order 8, whose band is one segment of 8 rows: alike; envelope, 40 problems of 215 x 182, order 32: 155 | 160 us).
 int axis_split(const fdetd_plan_t P)
 {
     if (std::getenv("FDETD_SEG_AXIS")) return 1;
     size_t cells = 0;
-    for (const Prob &q : P->probs) cells += q.cells;
+    int nd = 0;
+    for (const Prob &q : P->probs) {
+        cells += q.cells;
+        nd = std::max(nd, q.nd);
+    }
     const size_t small = P->kind == FDETD_MAXWELL ? (size_t)1 << 18 : (size_t)1 << 20;
-    return cells < small ? 4 : cells < 2 * small ? 2 : 1;
+    const size_t two = P->kind == FDETD_ENVELOPE && nd > 12 ? small + small / 4 : 2 * small;
+    return cells < small ? 4 : cells < two ? 2 : 1;
 }
 
 // FDETD_ENV_FUSE = 0 or 1 fixes whether envelope steps run in fused groups of stages; -1: unset.
