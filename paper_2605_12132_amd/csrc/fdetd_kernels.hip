@@ -1899,14 +1899,10 @@ __global__ __launch_bounds__(GATHER_BLOCK) __attribute__((amdgpu_waves_per_eu(4)
         row[v] = min(max(q, rlo), rhi) - rlo;
         below[v] = k < 0;
     }
-    // The planes in order of component, then mode: a component's sum goes on from one pass to the next (mode by mode
-    // all six went on, and 3 10^5 samples in one cell, three modes, took 79 us instead of 70).
-    // cr + i ci = e^(i mp theta).
-    double acc = 0.0, cr = 1.0, ci = 0.0;
-    int mp = 0;
-    const int inv = __builtin_amdgcn_readfirstlane((65536 + A.nprob - 1) / A.nprob);
-    // q / nprob for q < 6 nprob, nprob <= kMaxGather = 16 (a division per plane cost 2 % of the kernel)
-    auto component = [&](int q) { return q * inv >> 16; };
+    // The planes in order of mode, then component (the loop over the components unrolled, so that each adds to its own
+    // sum: with a sum selected by the component 3 10^5 samples in one cell, three modes, took 79 us instead of 70);
+    // cr + i ci = e^(i m theta) of the mode.
+    double acc[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0}, cr = 1.0, ci = 0.0;
     const int step = use_tile ? fit : npl;
 #pragma unroll 1
     for (int q0 = 0; q0 < npl; q0 += step) {
@@ -1914,72 +1910,82 @@ __global__ __launch_bounds__(GATHER_BLOCK) __attribute__((amdgpu_waves_per_eu(4)
         if (use_tile) {
             if (q0) __syncthreads();  // the last pass's reads are done
             const int per = tz * tr;
-            auto copy = [&](int q, int cell) {
-                const int k = cell / tz, i = cell % tz;
-                const V v = ((const V *)A.plane[q - component(q) * A.nprob][component(q)])[(size_t)(fp[2] + k) * A.nz + fp[0] + i];
-                tile[((q - q0) * tr + k) * ts + i] = double2{(double)v.x, (double)v.y};
-            };
-            if (fit == npl)  // small planes: the block's threads over all of them at once
-                for (int e = threadIdx.x; e < per * npl; e += GATHER_BLOCK) copy(e / per, e % per);
-            else
-                for (int q = q0; q < q1; ++q)
-                    for (int e = threadIdx.x; e < per; e += GATHER_BLOCK) copy(q, e);
+            const size_t first = (size_t)fp[2] * A.nz + fp[0];
+            if (fit == npl) {  // small planes: the block's threads over all of them at once
+                for (int e = threadIdx.x; e < per * npl; e += GATHER_BLOCK) {
+                    const int q = e / per, cell = e % per, k = cell / tz, i = cell % tz;
+                    const V v = ((const V *)A.plane[q / 6][q % 6])[first + (size_t)k * A.nz + i];
+                    tile[(q * tr + k) * ts + i] = double2{(double)v.x, (double)v.y};
+                }
+            } else {
+                for (int q = q0; q < q1; ++q) {
+                    const V *f = (const V *)A.plane[q / 6][q % 6] + first;
+                    for (int e = threadIdx.x; e < per; e += GATHER_BLOCK) {
+                        const int k = e / tz, i = e % tz;
+                        const V v = f[(size_t)k * A.nz + i];
+                        tile[((q - q0) * tr + k) * ts + i] = double2{(double)v.x, (double)v.y};
+                    }
+                }
+            }
             __syncthreads();
         }
         if (!live) continue;
 #pragma unroll 1
-        for (int q = q0; q < q1; ++q) {
-            const int c = component(q), p = q - c * A.nprob, m = A.m[p];
-            if (m < mp) {  // else on from the mode before
+        for (int p = q0 / 6; 6 * p < q1; ++p) {
+            const int m = A.m[p];
+            if (q0 <= 6 * p) {
                 cr = 1.0;
                 ci = 0.0;
-                mp = 0;
-            }
-            for (; mp < m; ++mp) {
-                const double t = cr * c1 - ci * s1;
-                ci = cr * s1 + ci * c1;
-                cr = t;
+                for (int j = 0; j < m; ++j) {
+                    const double t = cr * c1 - ci * s1;
+                    ci = cr * s1 + ci * c1;
+                    cr = t;
+                }
             }
             const double pS = (m % 2 == 0) ? 1.0 : -1.0, pA = ((m > 1 ? m - 1 : 1 - m) % 2 == 0) ? 1.0 : -1.0;
-            const double par = (c == 2 || c == 5) ? pS : pA;
-            double re = 0.0, im = 0.0;
 #pragma unroll
-            for (int a = 0; a < 4; ++a) {
-                const double wa = below[a] ? par * wr[a] : wr[a];
-                double v[8];
-                if (use_tile) {
-                    const double2 *t = tile + ((q - q0) * tr + row[a]) * ts;
+            for (int c = 0; c < 6; ++c) {
+                const int q = 6 * p + c;
+                if (q < q0 || q >= q1) continue;
+                const double par = (c == 2 || c == 5) ? pS : pA;
+                double re = 0.0, im = 0.0;
+#pragma unroll
+                for (int a = 0; a < 4; ++a) {
+                    const double wa = below[a] ? par * wr[a] : wr[a];
+                    double v[8];
+                    if (use_tile) {
+                        const double2 *t = tile + ((q - q0) * tr + row[a]) * ts;
+#pragma unroll
+                        for (int b = 0; b < 4; ++b) {
+                            const double2 g = t[col[b]];
+                            v[2 * b] = g.x;
+                            v[2 * b + 1] = g.y;
+                        }
+                    } else {
+                        const V *f = (const V *)A.plane[p][c] + (size_t)row[a] * A.nz;
+#pragma unroll
+                        for (int b = 0; b < 4; ++b) {
+                            const V g = f[col[b]];
+                            v[2 * b] = g.x;
+                            v[2 * b + 1] = g.y;
+                        }
+                    }
+                    double rre = 0.0, rim = 0.0;
 #pragma unroll
                     for (int b = 0; b < 4; ++b) {
-                        const double2 g = t[col[b]];
-                        v[2 * b] = g.x;
-                        v[2 * b + 1] = g.y;
+                        rre += wz[b] * v[2 * b];
+                        rim += wz[b] * v[2 * b + 1];
                     }
-                } else {
-                    const V *f = (const V *)A.plane[p][c] + (size_t)row[a] * A.nz;
-#pragma unroll
-                    for (int b = 0; b < 4; ++b) {
-                        const V g = f[col[b]];
-                        v[2 * b] = g.x;
-                        v[2 * b + 1] = g.y;
-                    }
+                    re += wa * rre;
+                    im += wa * rim;
                 }
-                double rre = 0.0, rim = 0.0;
-#pragma unroll
-                for (int b = 0; b < 4; ++b) {
-                    rre += wz[b] * v[2 * b];
-                    rim += wz[b] * v[2 * b + 1];
-                }
-                re += wa * rre;
-                im += wa * rim;
-            }
-            acc += re * cr - im * ci;
-            if (p == A.nprob - 1) {
-                A.fields[6 * s + c] = acc;
-                acc = 0.0;
+                acc[c] += re * cr - im * ci;
             }
         }
     }
+    if (!live) return;
+#pragma unroll
+    for (int c = 0; c < 6; ++c) A.fields[6 * s + c] = acc[c];
 }
 
 // Interpolation on the doubled grid (2x supersampling, section 3.4; SS bit 0: z, bit 1: rho), one thread
