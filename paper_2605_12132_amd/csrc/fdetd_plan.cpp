@@ -66,6 +66,7 @@ struct Batch {
     int fused = 0;             // envelope: tiles of the fused launch (0: stage by stage)
     int fused_seg = 0;         // ... and their rows
     int fused_home = 0;        // ... also in a call's last step, where the state has to end in the caller's planes
+    int fused_sure = 0;        // ... by its shape alone, without timing
     int lane = 0;              // stream of the batch's launches: 0 = the plan's stream, l > 0 = lanes[l - 1]
     double dt;
     std::vector<int> members;  // user indices, in table order
@@ -822,8 +823,10 @@ int plan_fused(fdetd_plan_t P, Batch &b, const ProbDesc *D, int fuse)
     double formed = 0.0;
     for (int t = 0; t < b.count; ++t) formed += (double)nr[t] * ((nz[t] + oc - 1) / oc) * oc;
     if (force < 0 && (fuse < 0 ? formed > 1.45 * cells : fuse == 0)) return FDETD_OK;
+    // one grid that fills the blocks gains from env_fuse_cells on, its copies included (the table there)
+    b.fused_sure = b.count == 1 && formed <= 1.15 * cells;
     if (force > 0) fuse = 2;
-    if (fuse < 0) fuse = b.N > env_depth(b.nd) || cells >= (size_t)b.count << 20 ? 2 : 1;
+    if (fuse < 0) fuse = b.fused_sure || b.N > env_depth(b.nd) || cells >= (size_t)b.count << 20 ? 2 : 1;
     b.fused_home = fuse == 2;
     b.fused = tiles;
     // the tiles cover the rows segment by segment, each from column 0 on without gap or overlap
@@ -1004,8 +1007,9 @@ BatchArgs tuning_args(fdetd_plan_t P, const Batch &b, const std::vector<void *> 
 
 // Times the envelope steps of the batches that could run in fused groups, at their tuned segment length: stage by
 // stage, fused as in the middle of a call, and as a call of one step.  What a group saves depends on the shapes (the
-// share of a block's columns that lie in the grid, rows per segment, problems per copy); only timing tells.  The state
-// stands in scratch[p] (a, a_tilde, chi; zeros), ev: two events.
+// share of a block's columns that lie in the grid, rows per segment, problems per copy): except for one grid that
+// fills the blocks only timing tells (plans of such a grid, 4096 x 512, take 8.1 ms; 10.3 with it timed as well).
+// The state stands in scratch[p] (a, a_tilde, chi; zeros), ev: two events.
 int tune_fused(fdetd_plan_t P, const std::vector<void *> &scratch, hipEvent_t *ev, bool log)
 {
     const size_t nb = P->batches.size(), eb = elem_bytes(P->precision);
@@ -1030,6 +1034,10 @@ int tune_fused(fdetd_plan_t P, const std::vector<void *> &scratch, hipEvent_t *e
     for (size_t bi = 0; bi < nb; ++bi) {
         const Batch &b = P->batches[bi];
         if (!b.fused) continue;
+        if (b.fused_sure) {
+            best[bi] = 2;
+            continue;
+        }
         auto two_steps = [&](int how) -> int {
             for (int st = 0; st < 2; ++st) {
                 const int rc = how == 0 ? enqueue_envelope_batch(P, b, a.data(), at.data(), chi.data(), P->stream)
@@ -1057,6 +1065,7 @@ int tune_fused(fdetd_plan_t P, const std::vector<void *> &scratch, hipEvent_t *e
             std::fprintf(stderr, "fdetd autotune batch %zu envelope step: %.4f ms stage by stage, %.4f fused, %.4f fused "
                          "as a call of one step -> %d\n", bi, t[0], t[1], t[2], best[bi]);
     }
+    if (best == P->fuse) return FDETD_OK;
     P->fuse = best;
     return build_batches(P);
 }
