@@ -1784,8 +1784,8 @@ int gather_impl(fdetd_plan_t plan, void *const *psi, const double *samples, int6
         pS = (m % 2 == 0) ? 1 : -1;
         pA = (std::abs(m - 1) % 2 == 0) ? 1 : -1;
     };
-    int p = 0;
-    for (std::vector<int> before, now; p < np || !before.empty(); before.swap(now)) {
+    // problems p0 .. p - 1: those of the launch before
+    for (int p0 = 0, p = 0, p1; p < np || p0 < p; p0 = p1) {
         X.npass = 0;
         int sets = 0;
         auto set_of = [&](const Prob &q) {  // -1: both sets hold other widths
@@ -1799,13 +1799,12 @@ int gather_impl(fdetd_plan_t plan, void *const *psi, const double *samples, int6
             X.pass[X.npass++] = DestaggerPass{src, dst, rho, parity, extrapolate, 0, grow_r, set};
         };
         int pS, pA;
-        for (int b : before) {  // B_theta's rho passes of the launch before
+        for (int b = p0; b < p; ++b) {  // B_theta's rho passes of the launch before
             const Prob &q = plan->probs[b];
             parities(q.d.m, pS, pA);
             add(plane(q, q.buf[1], 0), plane(q, q.buf[0], BTH), 1, pA, q.d.m == 1, 0, set_of(q));
         }
-        now.clear();
-        for (; p < np && X.npass + 5 <= kMaxDestaggerPass; ++p) {
+        for (p1 = p; p < np && X.npass + 5 <= kMaxDestaggerPass; ++p) {
             const Prob &q = plan->probs[p];
             const int set = set_of(q);
             if (set < 0) break;
@@ -1817,7 +1816,6 @@ int gather_impl(fdetd_plan_t plan, void *const *psi, const double *samples, int6
             add(plane(q, psi[p], BZ), plane(q, q.buf[0], BZ), 1, pS, q.d.m == 0, 0, set);
             G.m[p] = q.d.m;
             for (int c = 0; c < 6; ++c) G.plane[p][c] = c == ETH ? plane(q, psi[p], ETH) : plane(q, q.buf[0], c);
-            now.push_back(p);
         }
         HIPCHK(plan, launch_destagger(prec, X, plan->stream));
     }
