@@ -1417,9 +1417,10 @@ __device__ __forceinline__ double2 ld2(const V *p, size_t q)
 
 // A block of CORR_COLS columns and ROWS rows holds the stencil's operand, ROWS + 2 N_D - 1 rows of it, in LDS, so that
 // a value is read and scaled once per block instead of 2 N_D times: reads from the L2 bounded it (2048 x 256, order 16,
-// FP64: 15.1 us, now 9.7 at 4.4 TB/s of what it has to move).  The same tile left k_corr_apply, which reads two and
-// writes two planes beside its operand, where it was (11.2 and 11.0 us).  Rows per block: small grids need the blocks,
-// and each wavefront its loads in one go.  us per step of two modes (N = 2) without a tile | 4, 8, 16 rows:
+// FP64: 15.1 us, now 9.8, 3.4 TB/s of the four planes it reads and writes).  The same tile left k_corr_apply, which
+// reads two and writes two planes beside its operand, where it was (11.2 and 11.0 us).  Rows per block: small grids
+// need the blocks, and each wavefront its loads in one go.  us per step of two modes (N = 2) without a tile | 4, 8, 16
+// rows:
 //    257 x 33,  order 2  FP64  58 |  58  59  62     FP32C  60 |  61  62  65
 //    611 x 149, order 4        91 |  89  91  93            87 |  86  88  90
 //   5000 x 20,  order 8        94 |  91  92  96            85 |  85  87  90
