@@ -259,6 +259,8 @@ FDETD_API int envelope_step(fdetd_plan_t plan, void *const *a, void *const *a_ti
  *   samples  device array of n x 4 doubles: z, x, y, charge * weight (normalised units), 8-byte aligned.
  *   vz       velocity along z (finite); eps in [0, 1] (0.5 in the paper).
  *   j_half   n_probs device pointers as for fdetd_step (3 planes each, the plan's precision).
+ * A sample at an infinite position, or one beyond the range of int in cells, deposits nothing; one whose z is not a
+ * number neither, and one whose x or y is not puts NaN into rows 0 .. 3 of its nodes (the other depositions alike).
  * Enqueue only.  The adds are atomic, so the order of the summation, and the last bits, vary between runs.
  * Blocks of 1024 consecutive samples whose shapes touch at most 4096 cells of a grid sum their adds in an
  * FP64 LDS tile first: samples given in position order (as PIC codes keep them) are much faster. */
@@ -280,14 +282,16 @@ FDETD_API int fdetd_deposit_jz(fdetd_plan_t plan, const double *samples, int64_t
  * these, the densities at the end
  * positions satisfy (rho+ - rho-)/dt + D_z^(+) J_z - rho_xy = 0.  A sample whose z shapes reach past a z
  * end is not deposited.  A sample moving more than 3 cells along z in dt (its integrated shape spans
- * more than 8 nodes) is deposited in full with global atomics, outside the LDS tiles.
+ * more than 8 nodes) is deposited in full with global atomics, outside the LDS tiles.  Rows that both half-step
+ * positions touch are joined in FP64 before they are stored, in either precision.
  *   samples  device array of n x 8 doubles: z, x, y, q w, v_x, v_y, v_z, unused; 8-byte aligned.
  *   eps      in [0, 1].
  *   j_half   n_probs device pointers to current blocks as for fdetd_step (3 planes, 4 with
  *            FDETD_PLAN_CURRENT_CORRECTION), the plan's precision.
  * Enqueue only; atomic adds.  Blocks of up to 1024 consecutive samples order their samples by cell, sum those of
  * one cell first and add the sums in an FP64 LDS tile where their shapes touch at most 1232 cells of a grid (1124
- * with rho_xy): position-ordered samples are much faster. */
+ * with rho_xy): position-ordered samples are much faster.  A sample with a value that is not a number or not finite
+ * is added by itself: what it gives shows at its own nodes only. */
 FDETD_API int fdetd_deposit_current(fdetd_plan_t plan, const double *samples, int64_t n, double eps,
                                     void *const *j_half);
 
