@@ -133,7 +133,8 @@ typedef struct {
     double profiled_bytes;       /* sum of their algorithmic HBM bytes                           */
     /* tiling of the first launch batch: rho rows per marching segment of the main launch and of the
      * FP32C near-axis launch (0 without one; small plans share a near-axis segment out over up to 4
-     * wavefronts, see tile_rows_axis), and the plan-time autotuning that picked them (0 ms: none) */
+     * wavefronts, see tile_rows_axis), and the plan-time autotuning that picked them (0 ms: none).
+     * Envelope steps that run several stages per launch use seg_rows where they run stage by stage */
     int32_t seg_rows, seg_rows_axis;
     double autotune_ms;
     int32_t streams;  /* streams a step call runs on: 1, or up to 4 when the plan has several launch batches */
